@@ -308,7 +308,10 @@ SLOS_API int fock_mode_expectations_backward_ex(slos_batch_t batch, const float*
  * photon number n_g) and owns the output block [out_off[g], out_off[g+1])
  * of length C(m+n_g-1, n_g), basis order.  The components' amplitudes use
  * the batch's configuration for SLOS_OP_AMPLITUDES (forward) and
- * SLOS_OP_AMPLITUDES_BACKWARD (adjoint).  Cost: one SLOS per component.
+ * SLOS_OP_AMPLITUDES_BACKWARD (adjoint).  Cost: one SLOS per component, or,
+ * when every group holds enough distinct components (the full Fock space, no
+ * kernel variant set for the op), one pass of the whole superposition through
+ * U photon by photon, sum_k N_k N_{n-k} m products per group.
  */
 typedef struct slos_superposition_s* slos_superposition_t;
 

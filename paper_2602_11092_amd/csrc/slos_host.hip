@@ -577,7 +577,8 @@ extern "C" int slos_batch_create(slos_plan_t plan, int B, const int32_t* occ_hos
     Bt->n_host.resize(B);
     Bt->off_host.assign(B + 1, 0);
     Bt->thr_off_host.assign(B + 1, 0);
-    std::vector<int32_t> modes((size_t)std::max(B, 1) * kMaxPhotons, 0);
+    std::vector<int32_t>& modes = Bt->modes_host;
+    modes.assign((size_t)std::max(B, 1) * kMaxPhotons, 0);
     std::vector<float> innorm(std::max(B, 1), 1.f);
     for (int b = 0; b < B; ++b) {
         int n = 0;
@@ -959,6 +960,13 @@ size_t sup_ws_parts(const slos_superposition_s& S, bool bwd, size_t* uc, size_t*
     return *uc + *a + *ga + *guc + align256(*amp);
 }
 
+// Dense inputs go photon by photon unless a kernel variant was set for the
+// components' op (which runs one simulation per component).
+bool dense_steps(const slos_superposition_s& S, int op) {
+    const Config& c = S.batch->cfg[op];
+    return S.dev.dense && c.variant == SLOS_VARIANT_AUTO && c.block == 0;
+}
+
 }  // namespace
 
 extern "C" int slos_superposition_create(slos_batch_t components, int G, const int64_t* group_off,
@@ -1002,8 +1010,41 @@ extern "C" int slos_superposition_create(slos_batch_t components, int G, const i
         delete S;
         return fail(SLOS_EUNSUPPORTED, "slos_superposition_create: too many components for one launch");
     }
+    // dense inputs: every group has enough distinct components for the
+    // photon-by-photon steps to take fewer products than one simulation each
+    std::vector<int32_t> crank(std::max(Bt.B, 1), 0);
+    std::vector<float> cnorm(std::max(Bt.B, 1), 1.f);
+    std::vector<uint32_t> gcols(std::max(G, 1), 0u);
+    bool dense = G > 0;
+    std::vector<Counter> ranks;
+    for (int n = 0; n <= Bt.n_max && dense; ++n) ranks.emplace_back(Bt.plan->m, n);
+    for (int g = 0; g < G && dense; ++g) {
+        const int64_t c0 = group_off[g], c1 = group_off[g + 1];
+        const int n = Bt.n_host[c0];
+        dense = c1 - c0 <= Bt.plan->N[n] && dense_superposition_ok(*Bt.plan, n, c1 - c0);
+        if (!dense) break;
+        S->dev.n_present |= 1u << n;
+        const Counter& C = ranks[n];
+        std::vector<char> seen((size_t)Bt.plan->N[n], 0);
+        for (int64_t c = c0; c < c1; ++c) {
+            const int32_t* L = &Bt.modes_host[(size_t)c * kMaxPhotons];
+            crank[c] = (int32_t)C.rank(L, n);
+            double f = 1.0;
+            int run = 1;
+            for (int p = 0; p < n; ++p) {
+                run = p > 0 && L[p] == L[p - 1] ? run + 1 : 1;
+                f *= run;
+                gcols[g] |= 1u << L[p];
+            }
+            cnorm[c] = (float)std::sqrt(f);
+            if (seen[crank[c]]++) dense = false;  // repeated states: summed component by component
+        }
+    }
+    S->dev.dense = dense;
     const size_t o_grp = 0, o_goff = align256((size_t)std::max(Bt.B, 1) * 4), o_ooff = o_goff + align256((G + 1) * 8);
-    const size_t total = o_ooff + align256((G + 1) * 8);
+    const size_t o_cr = o_ooff + align256((G + 1) * 8), o_cn = o_cr + align256(crank.size() * 4);
+    const size_t o_gc = o_cn + align256(cnorm.size() * 4);
+    const size_t total = o_gc + align256(gcols.size() * 4);
     if (hipMalloc(&S->dmem, total) != hipSuccess) {
         delete S;
         return fail(SLOS_ENOMEM, "slos_superposition_create: hipMalloc failed");
@@ -1012,6 +1053,9 @@ extern "C" int slos_superposition_create(slos_batch_t components, int G, const i
     hipError_t e = hipMemcpy(base + o_grp, group.data(), group.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(base + o_goff, S->goff.data(), (G + 1) * 8, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(base + o_ooff, S->ooff.data(), (G + 1) * 8, hipMemcpyHostToDevice);
+    if (e == hipSuccess && dense) e = hipMemcpy(base + o_cr, crank.data(), crank.size() * 4, hipMemcpyHostToDevice);
+    if (e == hipSuccess && dense) e = hipMemcpy(base + o_cn, cnorm.data(), cnorm.size() * 4, hipMemcpyHostToDevice);
+    if (e == hipSuccess && dense) e = hipMemcpy(base + o_gc, gcols.data(), gcols.size() * 4, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         hipFree(S->dmem);
         delete S;
@@ -1021,6 +1065,9 @@ extern "C" int slos_superposition_create(slos_batch_t components, int G, const i
     S->dev.group = (const int32_t*)(base + o_grp);
     S->dev.goff = (const int64_t*)(base + o_goff);
     S->dev.ooff = (const int64_t*)(base + o_ooff);
+    S->dev.crank = (const int32_t*)(base + o_cr);
+    S->dev.cnorm = (const float*)(base + o_cn);
+    S->dev.gcols = (const uint32_t*)(base + o_gc);
     S->dev.max_n_states = maxN;
     *out = S;
     return SLOS_OK;
@@ -1065,6 +1112,9 @@ extern "C" int fock_superposition_amplitudes(slos_superposition_t sup, const flo
     void* rest = base + uc + a;
     hipStream_t s = (hipStream_t)stream;
     const slos_batch_s& Bt = *sup->batch;
+    if (dense_steps(*sup, SLOS_OP_AMPLITUDES))
+        return launch_dense_superposition(sup->dev, Bt, false, (const float2*)U, (const float2*)x, nullptr,
+                                          (float2*)out, nullptr, s);
     int rc = launch_superposition(kSupReplicateU, sup->dev, Bt, U, nullptr, nullptr, Uc, s);
     if (rc == SLOS_OK) rc = run(sup->batch, SLOS_OP_AMPLITUDES, (const float*)Uc, nullptr, A, rest, amp, stream);
     if (rc == SLOS_OK) rc = launch_superposition(kSupCombine, sup->dev, Bt, x, A, nullptr, out, s);
@@ -1090,6 +1140,9 @@ extern "C" int fock_superposition_amplitudes_backward(slos_superposition_t sup, 
     void* rest = base + uc + a + ga + guc;
     hipStream_t s = (hipStream_t)stream;
     const slos_batch_s& Bt = *sup->batch;
+    if (dense_steps(*sup, SLOS_OP_AMPLITUDES_BACKWARD))
+        return launch_dense_superposition(sup->dev, Bt, true, (const float2*)U, (const float2*)x,
+                                          (const float2*)grad_out, (float2*)grad_U, (float2*)grad_x, s);
     int rc = launch_superposition(kSupReplicateU, sup->dev, Bt, U, nullptr, nullptr, Uc, s);
     if (rc == SLOS_OK && grad_x) {
         rc = run(sup->batch, SLOS_OP_AMPLITUDES, (const float*)Uc, nullptr, A, rest, amp, stream);

@@ -109,6 +109,7 @@ struct slos_batch_s {
     int B = 0;
     int n_max = 0;
     std::vector<int32_t> n_host;
+    std::vector<int32_t> modes_host;  // [B][kMaxPhotons] input photon modes, ascending
     std::vector<int64_t> off_host;
     std::vector<int64_t> thr_off_host;  // click-pattern output offsets
     void* dmem = nullptr;
@@ -185,10 +186,22 @@ struct SupDev {
     const int64_t* goff = nullptr;   // [G+1]
     const int64_t* ooff = nullptr;   // [G+1]
     int64_t max_n_states = 1;        // largest output block of a group
+    // dense inputs (slos_superpose.hip): set where every group qualifies
+    bool dense = false;
+    uint32_t n_present = 0;          // bit n: some group holds n photons
+    const int32_t* crank = nullptr;  // [C] basis rank of each component's state
+    const float* cnorm = nullptr;    // [C] sqrt(prod s!)
+    const uint32_t* gcols = nullptr; // [G] input modes the group's components use
 };
 enum { kSupReplicateU, kSupCombine, kSupExpand, kSupGradX, kSupGroupSum };
 int launch_superposition(int kind, const SupDev& S, const slos_batch_s& Bt, const void* a0, const void* a1,
                          const void* a2, void* out, hipStream_t stream);
+// ---- dense superpositions: slos_superpose.hip ----
+// whether an input of `comps` distinct n-photon components takes the dense steps
+bool dense_superposition_ok(const slos_plan_s& P, int n, int64_t comps);
+// forward: out = the groups' amplitudes; backward: out = dL/dU, gx = dL/dx or nullptr
+int launch_dense_superposition(const SupDev& S, const slos_batch_s& Bt, bool bwd, const float2* U, const float2* x,
+                               const float2* gy, float2* out, float2* gx, hipStream_t stream);
 // p[i] = |a[i]|^2 and its adjoint ga[i] = 2 gp[i] a[i], over n values
 int launch_abs2(int64_t n, const float2* a, float* p, hipStream_t stream);
 int launch_abs2_backward(int64_t n, const float2* a, const float* gp, float2* ga, hipStream_t stream);

@@ -1,0 +1,99 @@
+"""Dense amplitude-encoded inputs (the photon-by-photon steps) against the
+oracle: every output, dL/dU and dL/dx, at the edges of the rule's range."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+from gpu_util import DEV, rel_err, say, to_dev_c64, widen  # noqa: E402
+import torch  # noqa: E402
+from paper_2602_11092_amd import _binding as B  # noqa: E402
+
+# FP32: a result adds at most m products per photon, 2 n steps with the
+# adjoint, on values of the size of the result (random phases): 2^-24 sqrt(2 m n)
+# is below 1e-6 everywhere below; the suite's bounds for amplitudes and gradients
+A_TOL, G_RTOL = 1e-5, 1e-4
+
+
+def _run(m, n, G, keep, seed, n_max=None):
+    rng = np.random.default_rng(seed)
+    basis = O.fock_basis(m, n)
+    occ, off = [], [0]
+    for _ in range(G):
+        pick = rng.permutation(len(basis))[: max(1, int(len(basis) * keep))]
+        occ += [basis[i] for i in pick]
+        off.append(len(occ))
+    occ = np.asarray(occ, dtype=np.int32)
+    U = W.haar_unitaries(rng, G, m).astype(np.complex64)
+    x = (rng.standard_normal(len(occ)) + 1j * rng.standard_normal(len(occ))).astype(np.complex64)
+    for g in range(G):
+        x[off[g]:off[g + 1]] /= np.linalg.norm(x[off[g]:off[g + 1]])
+    say("dense superposition", m, n, G, keep)
+    batch = B.Batch(B.Plan(m, n_max or n), occ)
+    sup = B.Superposition(batch, off)
+    Ud, xd = to_dev_c64(U), torch.from_numpy(x).to(DEV)
+    out = B.fock_superposition_amplitudes(sup, Ud, xd)
+    gy = torch.from_numpy((rng.standard_normal(sup.out_len) + 1j * rng.standard_normal(sup.out_len))
+                          .astype(np.complex64)).to(DEV)
+    gU, gx = B.fock_superposition_amplitudes_backward(sup, Ud, xd, gy)
+    gU2, none = B.fock_superposition_amplitudes_backward(sup, Ud, xd, gy, need_grad_x=False)
+    torch.cuda.synchronize()
+    assert none is None and torch.equal(gU, gU2)
+    N = len(basis)
+    for g in range(G):
+        c = range(off[g], off[g + 1])
+        amps = {k: O.amplitudes(widen(U[g]), occ[k]) for k in c}
+        ref = sum(complex(x[k]) * amps[k] for k in c)
+        assert np.abs(out.cpu().numpy()[g * N:(g + 1) * N] - ref).max() <= A_TOL
+        Gg = gy.cpu().numpy()[g * N:(g + 1) * N].astype(np.complex128)
+        ref_x = np.array([np.vdot(amps[k], Gg) for k in c])
+        assert rel_err(gx.cpu().numpy()[off[g]:off[g + 1]], ref_x) <= G_RTOL
+        ref_U = sum(O.amplitude_grad(widen(U[g]), occ[k], np.conj(complex(x[k])) * Gg) for k in c)
+        assert rel_err(gU.cpu().numpy()[g], ref_U) <= G_RTOL
+    return batch, sup
+
+
+@pytest.mark.parametrize("m,n,G,keep", [(2, 1, 3, 1.0), (3, 2, 5, 1.0), (6, 3, 4, 1.0), (6, 3, 5, 0.7), (5, 4, 2, 1.0),
+                                        (12, 2, 2, 1.0), (8, 3, 1, 1.0)])
+def test_dense_superposition_against_oracle(m, n, G, keep):
+    _run(m, n, G, keep, 17 * m + n)
+
+
+def test_dense_steps_match_one_simulation_per_component():
+    m, n, G = 6, 3, 9
+    rng = np.random.default_rng(3)
+    occ = np.tile(O.fock_basis(m, n), (G, 1)).astype(np.int32)
+    N = len(occ) // G
+    batch = B.Batch(B.Plan(m, n), occ)
+    sup = B.Superposition(batch, np.arange(G + 1) * N)
+    U = to_dev_c64(W.haar_unitaries(rng, G, m))
+    x = torch.randn(G * N, dtype=torch.complex64, device=DEV)
+    gy = torch.randn(G * N, dtype=torch.complex64, device=DEV)
+    a = (B.fock_superposition_amplitudes(sup, U, x), *B.fock_superposition_amplitudes_backward(sup, U, x, gy))
+    for op in (B.OP_AMPLITUDES, B.OP_AMPLITUDES_BACKWARD):
+        batch.set_config(op, B.VARIANT_FUSED, 256)
+    b = (B.fock_superposition_amplitudes(sup, U, x), *B.fock_superposition_amplitudes_backward(sup, U, x, gy))
+    for p, q in zip(a, b):
+        assert not torch.equal(p, q)  # two routes
+        assert rel_err(p.cpu().numpy(), q.cpu().numpy()) <= 1e-5
+
+
+def test_columns_no_component_uses_are_not_read():
+    # components of modes 0 and 1 only, enough of them for the dense steps; the
+    # other columns of U hold NaN and get a zero gradient
+    m, n = 2, 3
+    basis = O.fock_basis(2, n)
+    occ = np.zeros((len(basis), 3), dtype=np.int32)
+    occ[:, :m] = basis
+    batch = B.Batch(B.Plan(3, n), occ)
+    sup = B.Superposition(batch, [0, len(occ)])
+    U = W.haar_unitaries(np.random.default_rng(1), 1, 3).astype(np.complex64)
+    U[0, :, 2] = np.nan
+    x = torch.randn(len(occ), dtype=torch.complex64, device=DEV)
+    out = B.fock_superposition_amplitudes(sup, to_dev_c64(U), x)
+    gU, gx = B.fock_superposition_amplitudes_backward(sup, to_dev_c64(U), x, torch.ones_like(out))
+    assert torch.isfinite(torch.view_as_real(out)).all() and torch.isfinite(torch.view_as_real(gx)).all()
+    assert torch.isfinite(torch.view_as_real(gU)).all() and torch.count_nonzero(gU[:, :, 2]) == 0
