@@ -410,9 +410,10 @@ SLOS_API int fock_threshold_probs_backward(slos_batch_t batch, const float* U, c
  * transform of the caller's uniforms u (device, float, [B][S], in [0, 1)):
  * the first state whose cumulative probability exceeds u * sum(p), the last
  * state if none does.  p comes from the configuration set for
- * SLOS_OP_SAMPLE; its cumulative sums are formed in FP64 in the workspace
- * (slos_workspace_bytes(batch, SLOS_OP_SAMPLE) bytes) in a fixed order, so
- * equal uniforms give equal shots.  S >= 0. */
+ * SLOS_OP_SAMPLE; its cumulative sums are formed in FP64 in a fixed order, so
+ * equal uniforms give equal shots (on chip for samples of up to 131072
+ * states, else in the workspace; slos_workspace_bytes(batch, SLOS_OP_SAMPLE)
+ * bytes either way).  S >= 0. */
 SLOS_API int fock_sample(slos_batch_t batch, const float* U, const float* u, int S, int32_t* shots,
                          void* ws, size_t ws_bytes, void* stream);
 

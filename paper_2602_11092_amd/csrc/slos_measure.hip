@@ -232,6 +232,83 @@ __global__ __launch_bounds__(kMeasureBlock) void sample_kernel(BatchDev Bt, cons
     shots[i] = (int32_t)lo;
 }
 
+// Shots without the cumulative sums in memory, for samples of up to
+// kDirectStates states: workgroup (b, part) sums p over runs of kRun states
+// (FP64), scans the run sums in LDS, and each of its shots finds its run there
+// and walks the run's states from p.  Bound by reading p (twice over the L2:
+// once in order, one 64-byte run per shot); the sums that the passes above
+// write and the search reads back are 8 bytes a state.  m = 20, n = 5, B = 512,
+// S = 1024: 39 us; the three passes that form the sums in memory took 165.
+constexpr int kRun = 16;
+constexpr int kDirectBlock = 1024;
+constexpr int64_t kDirectStates = (int64_t)kRun * 8192;  // run sums within 64 KB of LDS
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+__global__ __launch_bounds__(kDirectBlock) void sample_direct_kernel(BatchDev Bt, const float* __restrict__ p,
+                                                                     const float* __restrict__ u, int S, int parts,
+                                                                     int32_t* __restrict__ shots) {
+    constexpr int kWaves = kDirectBlock / 64;
+    extern __shared__ double runs[];  // [R]: cumulative sums at the runs' ends
+    __shared__ double wtot[kWaves];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int b = blockIdx.x / parts, part = blockIdx.x % parts;
+    const int64_t off = ldg(Bt.off + b);
+    const int N = (int)(ldg(Bt.off + b + 1) - off);
+    const float* pb = p + off;
+    const int R = (N + kRun - 1) / kRun;
+    for (int r = tid; r < R; r += kDirectBlock) {
+        double v = 0.0;
+        if ((r + 1) * kRun <= N) {
+            f4u x[kRun / 4];
+#pragma unroll
+            for (int i = 0; i < kRun / 4; ++i) x[i] = *(const f4u*)(pb + r * kRun + 4 * i);
+#pragma unroll
+            for (int i = 0; i < kRun; ++i) v += (double)x[i / 4][i % 4];
+        } else {
+            for (int t = r * kRun; t < N; ++t) v += (double)pb[t];
+        }
+        runs[r] = v;
+    }
+    __syncthreads();
+    // inclusive scan: each thread its own stretch, then over the threads
+    const int each = (R + kDirectBlock - 1) / kDirectBlock;
+    const int lo = min(tid * each, R), hi = min(lo + each, R);
+    double x = 0.0;
+    for (int r = lo; r < hi; ++r) x += runs[r];
+    const double own = x;
+    for (int s = 1; s < 64; s <<= 1) {
+        const double y = __shfl_up(x, s, 64);
+        if (lane >= s) x += y;
+    }
+    if (lane == 63) wtot[w] = x;
+    __syncthreads();
+    double acc = x - own;
+    for (int q = 0; q < w; ++q) acc += wtot[q];
+    for (int r = lo; r < hi; ++r) {
+        acc += runs[r];
+        runs[r] = acc;
+    }
+    __syncthreads();
+    const double total = runs[R - 1];
+    for (int i = part * kDirectBlock + tid; i < S; i += parts * kDirectBlock) {
+        const double target = (double)u[(int64_t)b * S + i] * total;
+        int a = 0, e = R - 1;  // the first run that ends above the target, the last if none does
+        while (a < e) {
+            const int mid = (a + e) / 2;
+            if (runs[mid] > target) e = mid;
+            else a = mid + 1;
+        }
+        double c = a > 0 ? runs[a - 1] : 0.0;
+        const int t1 = min((a + 1) * kRun, N) - 1;
+        int t = a * kRun;
+        for (; t < t1; ++t) {
+            c += (double)pb[t];
+            if (c > target) break;
+        }
+        shots[(int64_t)b * S + i] = t;
+    }
+}
+
 // ---- amplitude-encoded inputs: components c in [goff[g], goff[g+1]) of group g
 
 // Uc[c] = U[group[c]]
@@ -388,6 +465,21 @@ int launch_threshold_scatter(const slos_batch_s& Bt, const float* gP, float* gp,
 
 int launch_sample(const slos_batch_s& Bt, const float* p, double* part, double* cdf, const float* u, int S,
                   int32_t* shots, hipStream_t stream) {
+    const int64_t Nmax = Bt.plan->N[Bt.n_max];
+    if (Nmax <= kDirectStates) {
+        if (S == 0) return SLOS_OK;
+        // a workgroup per sample, more where samples alone leave CUs idle (each
+        // then sums its sample again), never with fewer shots than threads
+        const int64_t fill = std::max<int64_t>(1, 2 * (int64_t)std::max(Bt.plan->num_cu, 1) / Bt.B);
+        int parts = (int)std::min<int64_t>(fill, ((int64_t)S + kDirectBlock - 1) / kDirectBlock);
+        const size_t lds = (size_t)((Nmax + kRun - 1) / kRun) * sizeof(double);
+        (void)hipFuncSetAttribute((void*)&sample_direct_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        void* args[] = {(void*)&Bt.dev, (void*)&p, (void*)&u, (void*)&S, (void*)&parts, (void*)&shots};
+        hipError_t e = hipLaunchKernel((void*)&sample_direct_kernel, dim3((unsigned)(Bt.B * parts)), dim3(kDirectBlock),
+                                       args, lds, stream);
+        if (e != hipSuccess) return fail(SLOS_EHIP, std::string("fock_sample launch: ") + hipGetErrorString(e));
+        return SLOS_OK;
+    }
     int C = (int)mode_expect_chunks(Bt);
     if ((int64_t)Bt.B * C >= ((int64_t)1 << 31)) return fail(SLOS_EUNSUPPORTED, "fock_sample: batch too large");
     if (((int64_t)Bt.B * S + kMeasureBlock - 1) / kMeasureBlock >= ((int64_t)1 << 31))
