@@ -1190,8 +1190,15 @@ bool fused_bwd_supported(const slos_plan_s& P, int n_max, int block, std::string
 int fused_default_block(const slos_plan_s& P, int n_max, bool backward) {
     if (backward) {
         const int64_t Np = n_max >= 2 ? P.N[n_max - 1] : 1;
-        // restricted spaces have adjoint instances at 256 and 512 threads only
-        return Np <= 1024 ? 256 : (Np <= 5120 || P.m > 20 || restricted_plan(P)) ? 512 : 768;
+        // restricted spaces have adjoint instances at 256 and 512 threads only,
+        // more than 20 modes none above 512
+        if (Np <= 1024) return 256;
+        if (Np <= 2048 || P.m > 20 || restricted_plan(P)) return 512;
+        // layer n-1 of 2049 to 5120 states, us at 512 / 768 / 1024 threads: m = 14,
+        // n = 5 (2380) B = 512 76.7 / 74.4 / 71.7; m = 16, n = 5 (3876) 101 / 98 / 94;
+        // m = 12, n = 2 to 6 (4368) B = 4096 343 / 324 / 324; one below, m = 13, n = 5
+        // (1820) 62.1 / 71.0 / 69.6.  Above 5120, m = 18, n = 5 (5985) 293 / 139 / 140
+        return Np <= 5120 ? 1024 : 768;
     }
     const int64_t Nbig = n_max >= 1 ? P.N[n_max] : 1;
     return Nbig >= 8192 ? 1024 : 256;

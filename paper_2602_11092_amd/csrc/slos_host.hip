@@ -714,12 +714,36 @@ int fused_block_for(const slos_batch_s& Bt, int op) {
     return blk;
 }
 
+// Whether AUTO takes the two-sample kernel for an op that writes amplitudes or
+// probabilities (the results are the one-sample kernel's bit for bit).  It
+// halves the LDS reads but also the workgroups, so it needs more samples than
+// CUs, and layers long enough to fill 1024 threads.  Both sides measured, us,
+// one sample per workgroup against two: m = 20, n = 5 (42504 outputs) B = 512
+// 57.9 / 39.1, B = 260 52.8 / 33.4; m = 18, n = 5 (26334) B = 300 39.1 / 25.0, but
+// B = 200 21.3 / 23.8; m = 12, n = 2 to 6 (12376) B = 4096 98 / 68; m = 14, n = 5
+// (8568) B = 512 21.0 / 14.2; m = 12, n = 5 (4368) B = 512 13.0 / 11.1; unbunched
+// m = 17, n = 5 (6188) B = 1000 21.9 / 23.2; m = 10, n = 5 (2002) B = 1024 11.4 / 16.7.
+bool auto_pairs(const slos_batch_s& Bt, int op) {
+    const slos_plan_s& P = *Bt.plan;
+    if (op != SLOS_OP_AMPLITUDES && op != SLOS_OP_PROBS && op != SLOS_OP_SAMPLE) return false;
+    const int64_t top = P.N[Bt.n_max];
+    return Bt.B > P.num_cu && (top >= 8192 || (top >= 4096 && Bt.B <= 2 * P.num_cu)) &&
+           fused_pairs_supported(P, Bt.n_max, 1024, nullptr);
+}
+
+// Last-layer tile of the two-sample kernel for an op.
+int pairs_tile(const slos_batch_s& Bt, int op) {
+    const Config& c = Bt.cfg[op];
+    return c.tile != 0 ? c.tile : c.variant == SLOS_VARIANT_AUTO ? 2 : 4;
+}
+
 // Resolves AUTO and the default block size for one op.
 int resolve(const slos_batch_s& Bt, int op, int* variant, int* block) {
     const slos_plan_s& P = *Bt.plan;
     const bool bwd = op_backward(op);
     Config c = Bt.cfg[op];
     int v = c.variant;
+    if (v == SLOS_VARIANT_AUTO && c.block == 0 && auto_pairs(Bt, op)) v = SLOS_VARIANT_FUSED_PAIRS;
     if (v == SLOS_VARIANT_AUTO) {
         const int blk = fused_block_for(Bt, op);
         const bool ok = bwd ? fused_bwd_supported(P, Bt.n_max, blk, nullptr)
@@ -802,7 +826,7 @@ extern "C" int slos_batch_get_config_ex(slos_batch_t batch, int op, int* variant
     if (!tile) return fail(SLOS_EINVAL, "slos_batch_get_config_ex: NULL argument");
     const int rc = slos_batch_get_config(batch, op, variant, block);
     if (rc != SLOS_OK) return rc;
-    *tile = batch->cfg[op].tile != 0 ? batch->cfg[op].tile : (*variant == SLOS_VARIANT_FUSED_PAIRS ? 4 : 0);
+    *tile = *variant == SLOS_VARIANT_FUSED_PAIRS ? pairs_tile(*batch, op) : 0;
     return SLOS_OK;
 }
 
@@ -858,7 +882,7 @@ int run_threshold(const slos_batch_s& Bt, int op, int v, int blk, const float* U
         // the fused variant sums the patterns inside the forward (p never leaves LDS)
         if (v == SLOS_VARIANT_FUSED && fused_threshold_supported(*Bt.plan, Bt.n_max, blk))
             return launch_fused_fwd(Bt, blk, (const float2*)U, out, 4, s);
-        rc = v == SLOS_VARIANT_FUSED_PAIRS ? launch_fused_pairs_fwd(Bt, blk, Bt.cfg[op].tile, (const float2*)U, pv, true, s)
+        rc = v == SLOS_VARIANT_FUSED_PAIRS ? launch_fused_pairs_fwd(Bt, blk, pairs_tile(Bt, op), (const float2*)U, pv, true, s)
              : fused                        ? launch_fused_fwd(Bt, blk, (const float2*)U, pv, 1, s)
                                             : launch_layered_fwd(Bt, blk, (const float2*)U, pv, true, rest, s);
         if (rc == SLOS_OK) rc = launch_threshold_gather(Bt, pv, (float*)out, s);
@@ -894,7 +918,7 @@ int run(slos_batch_t batch, int op, const float* U, const void* gin, void* out, 
     if (op_threshold(op)) return run_threshold(*batch, op, v, blk, U, gin, out, ws, ws_bytes, s, nm);
     int rc;
     if (v == SLOS_VARIANT_FUSED_PAIRS && !bwd) {
-        rc = launch_fused_pairs_fwd(*batch, blk, batch->cfg[op].tile, (const float2*)U, out, probs, s);
+        rc = launch_fused_pairs_fwd(*batch, blk, pairs_tile(*batch, op), (const float2*)U, out, probs, s);
     } else if (v == SLOS_VARIANT_FUSED) {
         rc = bwd ? launch_fused_bwd(*batch, blk, (const float2*)U, gin, probs, (float2*)out, s)
                  : launch_fused_fwd(*batch, blk, (const float2*)U, out, probs ? 1 : 0, s);
@@ -1354,7 +1378,7 @@ extern "C" int fock_sample(slos_batch_t batch, const float* U, const float* u, i
     double* cdf = (double*)(base + expect_head_bytes(*batch));
     double* part = (double*)(base + expect_head_bytes(*batch) + align256((size_t)batch->off_host[batch->B] * 8));
     hipStream_t s = (hipStream_t)stream;
-    int rc = v == SLOS_VARIANT_FUSED_PAIRS ? launch_fused_pairs_fwd(*batch, blk, batch->cfg[SLOS_OP_SAMPLE].tile, (const float2*)U, pv, true, s)
+    int rc = v == SLOS_VARIANT_FUSED_PAIRS ? launch_fused_pairs_fwd(*batch, blk, pairs_tile(*batch, SLOS_OP_SAMPLE), (const float2*)U, pv, true, s)
              : fused                        ? launch_fused_fwd(*batch, blk, (const float2*)U, pv, 1, s)
                                             : launch_layered_fwd(*batch, blk, (const float2*)U, pv, true, base + head, s);
     if (rc != SLOS_OK) return rc;
