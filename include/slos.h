@@ -269,18 +269,23 @@ SLOS_API int fock_probs_backward(slos_batch_t batch, const float* U, const float
 /* ---- Measurement: per-mode photon-number expectations (Sec. II-B) ------- */
 
 /* out (device, float, [B][m], sample order) <- <n_j> = sum_t t_j p_t over the
- * plan's output states (no renormalisation; for the full Fock space this
- * equals sum_i s_i |U[j][i]|^2).  The fused variant accumulates inside the
- * last photon layer and never writes p; the layered one writes p into the
- * workspace first.  ws: slos_workspace_bytes(batch, SLOS_OP_MODE_EXPECTATIONS)
- * bytes (the layered variant needs out_len * 4 bytes more than fock_probs).
+ * plan's output states (no renormalisation; for the full Fock space and a
+ * unitary U this equals sum_i s_i |U[j][i]|^2).  With the automatic variant,
+ * the full Fock space and at most 8 photons the sum is evaluated in closed
+ * form for any U (minors of the Gram matrix of U's input columns, FP64),
+ * whatever configuration is reported.  Otherwise the fused variant
+ * accumulates inside the last photon layer and never writes p; the layered
+ * one writes p into the workspace first.  ws:
+ * slos_workspace_bytes(batch, SLOS_OP_MODE_EXPECTATIONS) bytes (the layered
+ * variant needs out_len * 4 bytes more than fock_probs).
  * Works on restricted plans (SLOS_PLAN_UNBUNCHED, SLOS_PLAN_DUAL_RAIL). */
 SLOS_API int fock_mode_expectations(slos_batch_t batch, const float* U, float* out,
                                     void* ws, size_t ws_bytes, void* stream);
 
 /* grad_U (device, complex, [B][m][m]) <- dL/dU given grad_out = dL/d<n_j>
- * (device, float, [B][m]).  Forms dL/dp_t = sum_j t_j grad_out[b][j] in the
- * workspace (out_len floats) and runs the probability adjoint with the
+ * (device, float, [B][m]): in closed form where the forward is (the same
+ * conditions on its own op), else it forms dL/dp_t = sum_j t_j grad_out[b][j] in
+ * the workspace (out_len floats) and runs the probability adjoint with the
  * configuration set for SLOS_OP_MODE_EXPECTATIONS_BACKWARD.  Plans with
  * successor tables only (SLOS_EUNSUPPORTED otherwise). */
 SLOS_API int fock_mode_expectations_backward(slos_batch_t batch, const float* U, const float* grad_out,

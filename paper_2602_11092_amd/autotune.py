@@ -46,6 +46,10 @@ BACKWARD_CANDIDATES = [(B.VARIANT_FUSED, 256, 0), (B.VARIANT_FUSED, 512, 0), (B.
                        (B.VARIANT_FUSED, 1024, 0), (B.VARIANT_LAYERED, 128, 0), (B.VARIANT_LAYERED, 256, 0),
                        (B.VARIANT_LAYERED, 512, 0), (B.VARIANT_LAYERED, 1024, 0)]
 REFERENCE = (B.VARIANT_LAYERED, 256, 0)
+# ops whose default may take a route that no explicit variant names (per-mode
+# expectations of the full space need no Fock space)
+AUTO = (B.VARIANT_AUTO, 0, 0)
+_AUTO_OPS = (B.OP_MODE_EXPECTATIONS, B.OP_MODE_EXPECTATIONS_BACKWARD)
 _BACKWARD = (B.OP_AMPLITUDES_BACKWARD, B.OP_PROBS_BACKWARD, B.OP_MODE_EXPECTATIONS_BACKWARD,
              B.OP_THRESHOLD_PROBS_BACKWARD)
 GATE_SEED = 20260211
@@ -239,15 +243,21 @@ def autotune(batch: B.Batch, U: torch.Tensor, ops: Iterable[int] = (B.OP_PROBS, 
         hit = stored.get(str(op))
         if hit is not None:
             try:
-                batch.set_config(op, hit["variant"], hit["block"], hit.get("tile", 0))
+                if hit.get("auto"):
+                    batch.set_config(op, *AUTO)
+                else:
+                    batch.set_config(op, hit["variant"], hit["block"], hit.get("tile", 0))
                 report[op] = {"variant": hit["variant"], "block": hit["block"], "tile": hit.get("tile", 0),
                               "us": hit["us"], "cached": True, "timings": [], "rejected": []}
                 continue
             except B.SlosError:
                 pass  # the stored choice no longer applies: tune again
         cands = (candidates or {}).get(op) or (BACKWARD_CANDIDATES if op in _BACKWARD else FORWARD_CANDIDATES)
+        if op in _AUTO_OPS and not (candidates or {}).get(op):
+            cands = [AUTO, *cands]
         before = batch.get_config_ex(op)
         timings, rejected = [], []
+        auto_us = None
         for variant, block, tile in cands:
             try:
                 batch.set_config(op, variant, block, tile)
@@ -263,14 +273,19 @@ def autotune(batch: B.Batch, U: torch.Tensor, ops: Iterable[int] = (B.OP_PROBS, 
                 us = _time_us(fn, warmup, iters)
             except B.SlosError:
                 continue
+            if (variant, block, tile) == AUTO:  # listed as the configuration the library reports for it
+                variant, block, tile = batch.get_config_ex(op)
+                auto_us = us
             timings.append((variant, block, tile, us))
         if not timings:
             batch.set_config(op, *before)
             raise RuntimeError("autotune: no configuration runs op %d on this batch" % op)
         variant, block, tile, us = min(timings, key=lambda r: r[3])
-        batch.set_config(op, variant, block, tile)
+        auto = us == auto_us
+        batch.set_config(op, *(AUTO if auto else (variant, block, tile)))
         report[op] = {"variant": variant, "block": block, "tile": tile, "us": us, "cached": False,
                       "timings": timings, "rejected": rejected}
         if cache:
-            _store_cache(cache, key, op, {"variant": variant, "block": block, "tile": tile, "us": us})
+            _store_cache(cache, key, op, {"variant": variant, "block": block, "tile": tile, "us": us,
+                                          **({"auto": True} if auto else {})})
     return report

@@ -840,13 +840,18 @@ int run_expect(const slos_batch_s& Bt, int op, int v, int blk, const float* U, c
                void* ws, size_t ws_bytes, hipStream_t s, const std::string& nm, bool clicks) {
     const bool bwd = op == SLOS_OP_MODE_EXPECTATIONS_BACKWARD;
     const bool fused = v == SLOS_VARIANT_FUSED;
-    if (!bwd && fused) return launch_fused_fwd(Bt, blk, (const float2*)U, out, clicks ? 3 : 2, s);
+    // photon numbers of the full space need no Fock space (a variant set for the op takes the recursion)
+    const bool closed = !clicks && Bt.cfg[op].variant == SLOS_VARIANT_AUTO && Bt.cfg[op].block == 0 && expect_closed_ok(Bt);
+    if (!bwd && fused && !closed) return launch_fused_fwd(Bt, blk, (const float2*)U, out, clicks ? 3 : 2, s);
     // workspace: [p or dL/dp][partial sums (forward)][layered workspace]
     const size_t head = expect_head_bytes(Bt);
     const size_t parts = bwd ? 0 : align256(mode_expect_part_bytes(Bt));
-    const size_t need = head + parts + (fused ? 0 : layered_ws_bytes(Bt, bwd));
-    if (!ws || ws_bytes < need)
+    const size_t need = !bwd && fused ? 0 : head + parts + (fused ? 0 : layered_ws_bytes(Bt, bwd));
+    if (need > 0 && (!ws || ws_bytes < need))
         return fail(SLOS_EWORKSPACE, nm + ": workspace missing or too small (need " + std::to_string(need) + " bytes)");
+    if (closed)
+        return launch_expect_closed(Bt, bwd, (const float2*)U, (const float*)gin, bwd ? nullptr : (float*)out,
+                                    bwd ? (float2*)out : nullptr, s);
     float* pv = (float*)ws;
     void* rest = (char*)ws + head + parts;
     int rc;

@@ -158,6 +158,12 @@ int launch_layered_fwd(const slos_batch_s& Bt, int block, const float2* U, void*
 int launch_layered_bwd(const slos_batch_s& Bt, int block, const float2* U, const void* gin, bool probs,
                        float2* gU, void* ws, hipStream_t stream);
 
+// ---- expectations in closed form: slos_expect.hip ----
+bool expect_closed_ok(const slos_batch_s& Bt);
+// forward: out [B][m]; backward: gU from the gradient w of the expectations
+int launch_expect_closed(const slos_batch_s& Bt, bool bwd, const float2* U, const float* w, float* out, float2* gU,
+                         hipStream_t stream);
+
 // ---- measurement kernels: slos_measure.hip ----
 // States per workgroup in the measurement kernels' (sample, chunk) grids.
 constexpr int64_t kMeasureChunkStates = 16384;
