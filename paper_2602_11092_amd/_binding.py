@@ -8,6 +8,7 @@ fallback path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Tuple
 
@@ -139,15 +140,26 @@ def _check(fn: str, rc: int):
         raise SlosError(fn, rc, lib().slos_last_error().decode())
 
 
-def _stream_ptr(dev: torch.device):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+# The current stream's handle without building a Stream object (1.9 us a call,
+# twice per operation), where this torch has the call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+def _stream_ptr(dev: torch.device) -> int:
+    if _raw_stream is not None and dev.index is not None:
+        return _raw_stream(dev.index)
+    return torch.cuda.current_stream(dev).cuda_stream
+
+
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
 def _require(t: torch.Tensor, name: str, dtype, shape=None):
+    if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_cuda and (shape is None or t.shape == shape)
+            and t.is_contiguous() and not t.is_conj() and not t.is_neg()):
+        return
+    # which of them it is
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch.Tensor" % name)
     if not t.is_cuda:
@@ -183,8 +195,8 @@ class WorkspaceCache:
         return 1 << max(8, (max(int(nbytes), 1) - 1).bit_length())
 
     def get(self, key, nbytes: int, device) -> torch.Tensor:
-        dev = torch.device(device)
-        full = (key, str(dev))
+        dev = device if isinstance(device, torch.device) else torch.device(device)
+        full = (key, dev)
         ws = self._live.get(full)
         if ws is None or ws.numel() < nbytes:
             if ws is not None:
@@ -198,7 +210,7 @@ class WorkspaceCache:
 
 
 def _stream_key(device) -> int:
-    return int(torch.cuda.current_stream(torch.device(device)).cuda_stream)
+    return _stream_ptr(device if isinstance(device, torch.device) else torch.device(device))
 
 
 # ------------------------------------------------------------------ combinatorics
@@ -361,8 +373,8 @@ class Batch:
 
 def _ws_args(ws: Optional[torch.Tensor]):
     if ws is None:
-        return ctypes.c_void_p(0), 0
-    return ctypes.c_void_p(ws.data_ptr()), ws.numel()
+        return None, 0
+    return ws.data_ptr(), ws.numel()
 
 
 # ------------------------------------------------------------------ forward / backward
@@ -717,9 +729,14 @@ def mesh_workspace(m: int, B: int, device) -> torch.Tensor:
     """Workspace of the mesh calls on the current stream, shared by every
     caller on that stream and device; buffers that become too small are
     retired, never freed (WorkspaceCache)."""
+    return _mesh_ws.get(("mesh", _stream_key(device)), _mesh_bytes(m, B), device)
+
+
+@functools.lru_cache(maxsize=256)
+def _mesh_bytes(m: int, B: int) -> int:
     n = ctypes.c_size_t(0)
     _check("mesh_workspace_bytes", lib().mesh_workspace_bytes(m, B, ctypes.byref(n)))
-    return _mesh_ws.get(("mesh", _stream_key(device)), int(n.value), device)
+    return int(n.value)
 
 
 def mesh_to_unitary(theta: torch.Tensor, x: Optional[torch.Tensor], enc_scale: float, m: Optional[int] = None,

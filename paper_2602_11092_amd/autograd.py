@@ -15,6 +15,8 @@ from . import _binding as B
 def _dense(t: torch.Tensor, dtype) -> torch.Tensor:
     """Plain contiguous memory of t's values (autograd may hand over lazy
     conjugate or negative views, whose memory holds other values)."""
+    if t.dtype is dtype and t.is_contiguous() and not t.is_conj() and not t.is_neg():
+        return t
     return t.resolve_conj().resolve_neg().to(dtype).contiguous()
 
 
