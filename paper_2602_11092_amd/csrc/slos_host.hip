@@ -176,7 +176,7 @@ void parallel_ranges(int64_t total, F&& body) {
 struct HostLayer {
     std::vector<int32_t> pred, succ, minoff;
     std::vector<float> nrm;
-    std::vector<int32_t> thr_ptr, thr_idx;  // click-pattern tables (SLOS_PLAN_THRESHOLD)
+    std::vector<int32_t> thr_ptr, thr_idx, thr_pat;  // click-pattern tables (SLOS_PLAN_THRESHOLD)
     std::vector<int32_t> thr_chunk;         // runs of whole patterns of at most kThrChunkStates states
     std::vector<int32_t> thr_pred;          // packed pred rows in click-pattern order
     std::vector<float> thr_nrm;             // nrm in click-pattern order
@@ -245,7 +245,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // state: offset of its click count j plus the rank of its occupied modes
 // among the j-sets (unbunched order).
 void build_threshold(int m, int k, const Counter& Ck, int64_t Nk, std::vector<int32_t>& ptr,
-                     std::vector<int32_t>& idx) {
+                     std::vector<int32_t>& idx, std::vector<int32_t>& pat) {
     const int jmax = std::min(k, m);
     std::vector<int64_t> off(jmax + 2, 0);
     std::vector<Counter> sets;
@@ -253,7 +253,7 @@ void build_threshold(int m, int k, const Counter& Ck, int64_t Nk, std::vector<in
     for (int j = 0; j <= jmax; ++j) sets.emplace_back(m, j, 1);
     for (int j = 1; j <= jmax; ++j) off[j + 1] = off[j] + binom(m, j);
     const int64_t Q = off[jmax + 1];
-    std::vector<int32_t> pat(Nk);
+    pat.assign(Nk, 0);
     parallel_ranges(Nk, [&](int64_t lo, int64_t hi) {
         int L[kMaxPhotons], D[kMaxPhotons];
         Ck.unrank(lo, k, L);
@@ -450,7 +450,7 @@ extern "C" int slos_plan_create(int m, int n_max, int flags, slos_plan_t* out) {
         H[k].pred.swap(packed);
         shifts[k] = shift;
         if (flags & SLOS_PLAN_THRESHOLD) {
-            build_threshold(m, k, C[k], Nk, H[k].thr_ptr, H[k].thr_idx);
+            build_threshold(m, k, C[k], Nk, H[k].thr_ptr, H[k].thr_idx, H[k].thr_pat);
             // greedy runs of whole patterns (a pattern holds at most C(15, 7) states, fewer than a run)
             const int32_t Qk = (int32_t)H[k].thr_ptr.size() - 1;
             for (int32_t q0 = 0; q0 < Qk;) {
@@ -487,7 +487,7 @@ extern "C" int slos_plan_create(int m, int n_max, int flags, slos_plan_t* out) {
     // one device allocation for every table
     size_t total = align256(sizeof(LayerDev) * (n_max + 1));
     std::vector<size_t> o_pred(n_max + 1), o_succ(n_max + 1), o_nrm(n_max + 1), o_min(n_max + 1);
-    std::vector<size_t> o_tp(n_max + 1), o_ti(n_max + 1), o_tc(n_max + 1), o_tpr(n_max + 1), o_tnr(n_max + 1);
+    std::vector<size_t> o_tp(n_max + 1), o_ti(n_max + 1), o_tt(n_max + 1), o_tc(n_max + 1), o_tpr(n_max + 1), o_tnr(n_max + 1);
     for (int k = 1; k <= n_max; ++k) {
         o_pred[k] = total; total += align256(H[k].pred.size() * 4);
         o_succ[k] = total; total += align256(H[k].succ.size() * 4);
@@ -495,6 +495,7 @@ extern "C" int slos_plan_create(int m, int n_max, int flags, slos_plan_t* out) {
         o_min[k] = total;  total += align256(H[k].minoff.size() * 4);
         o_tp[k] = total;   total += align256(H[k].thr_ptr.size() * 4);
         o_ti[k] = total;   total += align256(H[k].thr_idx.size() * 4);
+        o_tt[k] = total;   total += align256(H[k].thr_pat.size() * 4);
         o_tc[k] = total;   total += align256(H[k].thr_chunk.size() * 4);
         o_tpr[k] = total;  total += align256(H[k].thr_pred.size() * 4);
         o_tnr[k] = total;  total += align256(H[k].thr_nrm.size() * 4);
@@ -521,6 +522,7 @@ extern "C" int slos_plan_create(int m, int n_max, int flags, slos_plan_t* out) {
         const bool thr = !H[k].thr_ptr.empty();
         L.thr_ptr = thr ? (const int32_t*)(base + o_tp[k]) : nullptr;
         L.thr_idx = thr ? (const int32_t*)(base + o_ti[k]) : nullptr;
+        L.thr_pat = thr ? (const int32_t*)(base + o_tt[k]) : nullptr;
         L.Q = thr ? (int64_t)H[k].thr_ptr.size() - 1 : 0;
         L.thr_chunk = thr ? (const int32_t*)(base + o_tc[k]) : nullptr;
         L.thr_nchunk = thr ? (int32_t)H[k].thr_chunk.size() - 1 : 0;
@@ -531,6 +533,8 @@ extern "C" int slos_plan_create(int m, int n_max, int flags, slos_plan_t* out) {
             e = hipMemcpy(base + o_tp[k], H[k].thr_ptr.data(), H[k].thr_ptr.size() * 4, hipMemcpyHostToDevice);
         if (e == hipSuccess && thr)
             e = hipMemcpy(base + o_ti[k], H[k].thr_idx.data(), H[k].thr_idx.size() * 4, hipMemcpyHostToDevice);
+        if (e == hipSuccess && thr)
+            e = hipMemcpy(base + o_tt[k], H[k].thr_pat.data(), H[k].thr_pat.size() * 4, hipMemcpyHostToDevice);
         if (e == hipSuccess && thr)
             e = hipMemcpy(base + o_tc[k], H[k].thr_chunk.data(), H[k].thr_chunk.size() * 4, hipMemcpyHostToDevice);
         if (e == hipSuccess && thr)

@@ -54,6 +54,7 @@ struct LayerDev {
     // thr_idx[thr_ptr[q] .. thr_ptr[q+1]), ascending
     const int32_t* thr_ptr; // [Q + 1]
     const int32_t* thr_idx; // [N]
+    const int32_t* thr_pat; // [N]: each state's click pattern
     int64_t Q;              // number of click patterns of k photons
     // the patterns cut into runs of whole patterns holding at most
     // kThrChunkStates states: run r is patterns [thr_chunk[r], thr_chunk[r+1])
