@@ -47,9 +47,10 @@ BACKWARD_CANDIDATES = [(B.VARIANT_FUSED, 256, 0), (B.VARIANT_FUSED, 512, 0), (B.
                        (B.VARIANT_LAYERED, 512, 0), (B.VARIANT_LAYERED, 1024, 0)]
 REFERENCE = (B.VARIANT_LAYERED, 256, 0)
 # ops whose default may take a route that no explicit variant names (per-mode
-# expectations of the full space need no Fock space)
+# expectations of the full space need no Fock space; spaces beyond LDS may be
+# evaluated from two halves of the modes)
 AUTO = (B.VARIANT_AUTO, 0, 0)
-_AUTO_OPS = (B.OP_MODE_EXPECTATIONS, B.OP_MODE_EXPECTATIONS_BACKWARD)
+_AUTO_OPS = (B.OP_AMPLITUDES, B.OP_PROBS, B.OP_MODE_EXPECTATIONS, B.OP_MODE_EXPECTATIONS_BACKWARD)
 _BACKWARD = (B.OP_AMPLITUDES_BACKWARD, B.OP_PROBS_BACKWARD, B.OP_MODE_EXPECTATIONS_BACKWARD,
              B.OP_THRESHOLD_PROBS_BACKWARD)
 GATE_SEED = 20260211

@@ -273,6 +273,44 @@ void build_threshold(int m, int k, const Counter& Ck, int64_t Nk, std::vector<in
     for (int64_t t = 0; t < Nk; ++t) idx[fill[pat[t]]++] = (int32_t)t;
 }
 
+// Tables of the two-halves evaluation for n photons of the full space.
+void build_halves(int m, int n, HalvesDev& D, std::vector<int32_t>& base, std::vector<int32_t>& minoff) {
+    D.n = n;
+    D.c = m / 2;
+    D.mh[0] = D.c;
+    D.mh[1] = m - D.c;
+    int64_t at = 0;
+    minoff.assign((size_t)2 * (kHalvesMaxN + 1) * (kMaxModes + 1), 0);
+    for (int s = 0; s < 2; ++s)
+        for (int l = 0; l <= n; ++l) {
+            D.D[s][l] = (int)space_dim(D.mh[s], l, 0);
+            D.toff[s][l] = at;
+            if (l > 0) at += (int64_t)binom(n, l) * D.D[s][l];
+            if (l == 0) continue;
+            const Counter C(D.mh[s], l);
+            for (int j = 0; j <= D.mh[s]; ++j)
+                minoff[((size_t)s * (kHalvesMaxN + 1) + l) * (kMaxModes + 1) + j] = (int32_t)C.below[l - 1][j];
+        }
+    D.per_sample = at;
+    for (int mu = 1; mu <= kHalvesMaxN; ++mu) D.rs[mu] = 1.0 / std::sqrt((double)mu);
+    const Counter Cn(m, n);
+    for (int k = 0; k <= n; ++k) {
+        D.boff[k] = (int)base.size();
+        base.resize(base.size() + D.D[0][k]);
+        int32_t* out = base.data() + D.boff[k];
+        const Counter lo(D.c, k);
+        parallel_ranges(D.D[0][k], [&](int64_t r0, int64_t r1) {
+            int L[kMaxPhotons + 1], F[kMaxPhotons];
+            if (k > 0) lo.unrank(r0, k, L);
+            for (int64_t r = r0; r < r1; ++r) {
+                for (int p = 0; p < n; ++p) F[p] = p < k ? L[p] : D.c;  // the first beta: all photons in mode c
+                out[r] = (int32_t)Cn.rank(F, n);
+                if (k > 0) lo.next(L, k);
+            }
+        });
+    }
+}
+
 }  // namespace
 
 int64_t threshold_dim(int m, int n) {
@@ -500,6 +538,16 @@ extern "C" int slos_plan_create(int m, int n_max, int flags, slos_plan_t* out) {
         o_tpr[k] = total;  total += align256(H[k].thr_pred.size() * 4);
         o_tnr[k] = total;  total += align256(H[k].thr_nrm.size() * 4);
     }
+    // the two-halves tables of the photon numbers whose layers the on-chip
+    // kernels cannot hold (4 bytes per low-half state of each level)
+    std::vector<int32_t> HB[kHalvesMaxN + 1], HM[kHalvesMaxN + 1];
+    size_t o_hb[kHalvesMaxN + 1] = {}, o_hm[kHalvesMaxN + 1] = {};
+    for (int n = kHalvesMinN; n <= std::min(n_max, kHalvesMaxN); ++n) {
+        if (group != 0 || m < 4 || P->N[n] < (n == 5 ? 100000 : 20000)) continue;
+        build_halves(m, n, P->halves[n], HB[n], HM[n]);
+        o_hb[n] = total; total += align256(HB[n].size() * 4);
+        o_hm[n] = total; total += align256(HM[n].size() * 4);
+    }
     if (hipMalloc(&P->dmem, total) != hipSuccess) {
         delete P;
         return fail(SLOS_ENOMEM, "slos_plan_create: hipMalloc of the transition tables failed");
@@ -547,6 +595,13 @@ extern "C" int slos_plan_create(int m, int n_max, int flags, slos_plan_t* out) {
             e = hipMemcpy(base + o_nrm[k], H[k].nrm.data(), H[k].nrm.size() * 4, hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = hipMemcpy(base + o_min[k], H[k].minoff.data(), H[k].minoff.size() * 4, hipMemcpyHostToDevice);
+    }
+    for (int n = 0; n <= kHalvesMaxN && e == hipSuccess; ++n) {
+        if (P->halves[n].n == 0) continue;
+        P->halves[n].base = (const int32_t*)(base + o_hb[n]);
+        P->halves[n].minoff = (const int32_t*)(base + o_hm[n]);
+        e = hipMemcpy(base + o_hb[n], HB[n].data(), HB[n].size() * 4, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(base + o_hm[n], HM[n].data(), HM[n].size() * 4, hipMemcpyHostToDevice);
     }
     P->d_layers = (LayerDev*)base;
     if (e == hipSuccess)
@@ -605,6 +660,7 @@ extern "C" int slos_batch_create(slos_plan_t plan, int B, const int32_t* occ_hos
         Bt->off_host[b + 1] = Bt->off_host[b] + plan->N[n];
         Bt->thr_off_host[b + 1] = Bt->thr_off_host[b] + threshold_dim(m, n);
         Bt->n_max = std::max(Bt->n_max, n);
+        Bt->n_min = b == 0 ? n : std::min(Bt->n_min, n);
     }
     std::vector<int32_t> order(B);
     std::iota(order.begin(), order.end(), 0);
@@ -741,6 +797,14 @@ int pairs_tile(const slos_batch_s& Bt, int op) {
     return c.tile != 0 ? c.tile : c.variant == SLOS_VARIANT_AUTO ? 2 : 4;
 }
 
+// Whether AUTO, which would run layer by layer, takes the two halves instead.
+bool auto_halves(const slos_batch_s& Bt, int op) {
+    if (op != SLOS_OP_AMPLITUDES && op != SLOS_OP_PROBS) return false;
+    const Config& c = Bt.cfg[op];
+    if (c.variant != SLOS_VARIANT_AUTO || c.block != 0 || !halves_ok(Bt)) return false;
+    return !fused_fwd_supported(*Bt.plan, Bt.n_max, fused_block_for(Bt, op), nullptr);
+}
+
 // Resolves AUTO and the default block size for one op.
 int resolve(const slos_batch_s& Bt, int op, int* variant, int* block) {
     const slos_plan_s& P = *Bt.plan;
@@ -771,7 +835,9 @@ extern "C" int slos_workspace_bytes(slos_batch_t batch, int op, size_t* bytes) {
     if (!op_valid(op)) return fail(SLOS_EINVAL, "slos_workspace_bytes: bad op");
     int v, blk;
     resolve(*batch, op, &v, &blk);
-    *bytes = variant_fused(v) ? 0 : layered_ws_bytes(*batch, op_backward(op));
+    *bytes = variant_fused(v)          ? 0
+             : auto_halves(*batch, op) ? halves_ws_bytes(*batch)
+                                       : layered_ws_bytes(*batch, op_backward(op));
     // the expectation forward keeps p and partial sums in the workspace only
     // when layered; the backward always keeps dL/dp
     if (op == SLOS_OP_MODE_EXPECTATIONS_BACKWARD) *bytes += expect_head_bytes(*batch);
@@ -932,12 +998,16 @@ int run(slos_batch_t batch, int op, const float* U, const void* gin, void* out, 
         rc = bwd ? launch_fused_bwd(*batch, blk, (const float2*)U, gin, probs, (float2*)out, s)
                  : launch_fused_fwd(*batch, blk, (const float2*)U, out, probs ? 1 : 0, s);
     } else {
-        const size_t need = layered_ws_bytes(*batch, bwd);
+        const bool halves = auto_halves(*batch, op);
+        const size_t need = halves ? halves_ws_bytes(*batch) : layered_ws_bytes(*batch, bwd);
         if (need > 0 && (!ws || ws_bytes < need))
             return fail(SLOS_EWORKSPACE, nm + ": workspace missing or too small (need " + std::to_string(need) +
                                              " bytes)");
-        rc = bwd ? launch_layered_bwd(*batch, blk, (const float2*)U, gin, probs, (float2*)out, ws, s)
-                 : launch_layered_fwd(*batch, blk, (const float2*)U, out, probs, ws, s);
+        if (halves)
+            rc = launch_halves_fwd(*batch, (const float2*)U, out, probs, ws, s);
+        else
+            rc = bwd ? launch_layered_bwd(*batch, blk, (const float2*)U, gin, probs, (float2*)out, ws, s)
+                     : launch_layered_fwd(*batch, blk, (const float2*)U, out, probs, ws, s);
     }
     return rc;
 }

@@ -86,6 +86,22 @@ struct BatchDev {
     int npairs;
 };
 
+// Two-halves evaluation (slos_halves.h) of n-photon spaces beyond LDS: level
+// sizes and tables of the low and high mode halves.
+constexpr int kHalvesMinN = 5, kHalvesMaxN = 8;  // photon numbers with compiled instances
+struct HalvesDev {
+    int n = 0;                            // 0: not served
+    int c = 0;                            // modes in the low half
+    int mh[2] = {};                       // modes of each half
+    int D[2][kHalvesMaxN + 1] = {};       // states of level l
+    int64_t toff[2][kHalvesMaxN + 1] = {};  // level l's factors [C(n, l)][D] within a sample's tables (complex values)
+    int64_t per_sample = 0;               // complex values of a sample's tables
+    int boff[kHalvesMaxN + 1] = {};       // first entry of k in base
+    double rs[kHalvesMaxN + 1] = {};      // rs[mu] = mu^(-1/2)
+    const int32_t* base = nullptr;        // per (k, alpha): rank of (alpha, first beta)
+    const int32_t* minoff = nullptr;      // [2][kHalvesMaxN + 1][kMaxModes + 1]: first row of level l whose first mode is >= j
+};
+
 struct Config {
     int variant = SLOS_VARIANT_AUTO;
     int block = 0;
@@ -103,12 +119,14 @@ struct slos_plan_s {
     void* dmem = nullptr;             // all tables, one allocation
     slos::LayerDev* d_layers = nullptr;  // device copy of layers[0..n_max]
     std::vector<slos::LayerDev> layers;  // host copy (device pointers)
+    slos::HalvesDev halves[slos::kHalvesMaxN + 1];  // by photon number
 };
 
 struct slos_batch_s {
     slos_plan_s* plan = nullptr;
     int B = 0;
     int n_max = 0;
+    int n_min = 0;
     std::vector<int32_t> n_host;
     std::vector<int32_t> modes_host;  // [B][kMaxPhotons] input photon modes, ascending
     std::vector<int64_t> off_host;
@@ -158,6 +176,12 @@ int launch_layered_fwd(const slos_batch_s& Bt, int block, const float2* U, void*
                        void* ws, hipStream_t stream);
 int launch_layered_bwd(const slos_batch_s& Bt, int block, const float2* U, const void* gin, bool probs,
                        float2* gU, void* ws, hipStream_t stream);
+
+// ---- two halves (workspace-resident, any size): slos_halves.hip ----
+// whether a batch (every sample the same photon number) can take it
+bool halves_ok(const slos_batch_s& Bt);
+size_t halves_ws_bytes(const slos_batch_s& Bt);
+int launch_halves_fwd(const slos_batch_s& Bt, const float2* U, void* out, bool probs, void* ws, hipStream_t stream);
 
 // ---- expectations in closed form: slos_expect.hip ----
 bool expect_closed_ok(const slos_batch_s& Bt);

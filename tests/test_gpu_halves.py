@@ -1,0 +1,81 @@
+"""Spaces beyond on-chip memory by the two halves of the modes (the default
+there) against the layer-by-layer recursion, every output: each compiled photon
+number, odd mode counts (unequal halves), the smallest batches that take it,
+bunched inputs; and the batches that keep the recursion."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+from gpu_util import rel_err, say, to_dev_c64  # noqa: E402
+import torch  # noqa: E402
+from paper_2602_11092_amd import _binding as B  # noqa: E402
+
+# FP32 on both sides: sums of up to 32 products per rounding chain, and n levels:
+# 2^-24 sqrt(32 + 2 n^2) = 8e-7 on either
+REL = 2e-6
+
+
+def _batch(m, n, Bn, seed):
+    rng = np.random.default_rng(seed)
+    U = W.haar_unitaries(rng, Bn, m).astype(np.complex64)
+    occ = np.zeros((Bn, m), dtype=np.int32)
+    for b in range(Bn):
+        np.add.at(occ[b], rng.choice(m, size=n, replace=b % 2 == 1), 1)
+    return to_dev_c64(U), occ
+
+
+@pytest.mark.parametrize("m,n,Bn", [(25, 5, 9), (18, 6, 10), (28, 6, 1), (14, 7, 26), (21, 7, 3), (12, 8, 40), (17, 8, 5)])
+def test_two_halves_match_the_recursion(m, n, Bn):
+    U, occ = _batch(m, n, Bn, 7 * m + n)
+    say("two halves", m, n, Bn)
+    batch = B.Batch(B.Plan(m, n), occ)
+    ref = B.Batch(batch.plan, occ)
+    for op in (B.OP_PROBS, B.OP_AMPLITUDES):
+        assert batch.get_config(op)[0] == B.VARIANT_LAYERED
+        ref.set_config(op, B.VARIANT_LAYERED, 256)
+    a, p = B.fock_amplitudes(batch, U), B.fock_probs(batch, U)
+    ra, rp = B.fock_amplitudes(ref, U), B.fock_probs(ref, U)
+    torch.cuda.synchronize()
+    assert not torch.equal(a, ra)  # two routes
+    for b in range(Bn):
+        o = slice(batch.offsets[b], batch.offsets[b + 1])
+        assert rel_err(a[o].cpu().numpy(), ra[o].cpu().numpy()) <= REL, b
+        assert rel_err(p[o].cpu().numpy(), rp[o].cpu().numpy()) <= REL, b
+        assert (p[o] - a[o].abs().square()).abs().max().item() <= 1e-6
+
+
+@pytest.mark.parametrize("few", [False, True])
+def test_mixed_photon_numbers_and_small_batches_keep_the_recursion(few):
+    m = 18
+    U, occ = _batch(m, 6, 12, 5)
+    occ[1] = 0
+    occ[1, :5] = 1
+    if few:
+        U, occ = U[:2].contiguous(), np.tile(occ[:1], (2, 1))
+    batch = B.Batch(B.Plan(m, 6), occ)
+    ref = B.Batch(batch.plan, occ)
+    ref.set_config(B.OP_PROBS, B.VARIANT_LAYERED, 0)
+    assert torch.equal(B.fock_probs(batch, U), B.fock_probs(ref, U))
+
+
+def test_two_halves_graph_replays():
+    m, n = 18, 6
+    U, occ = _batch(m, n, 10, 9)
+    batch = B.Batch(B.Plan(m, n), occ)
+    out = torch.empty(batch.out_len, dtype=torch.float32, device=U.device)
+    ws = batch.workspace(B.OP_PROBS, U.device)
+    B.fock_probs(batch, U, out=out, ws=ws)
+    torch.cuda.synchronize()
+    want = out.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.fock_probs(batch, U, out=out, ws=ws)
+    for _ in range(3):
+        out.zero_()
+        ws.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
