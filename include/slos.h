@@ -117,8 +117,8 @@ extern "C" {
 /* Kernel variants for slos_batch_set_config. */
 /* AUTO may also take routes that no other value names (the values below keep
  * the photon layers): per-mode expectations of the full space in closed form,
- * and the forward of large batches of 5 to 8 photons, every sample alike,
- * beyond LDS, from two halves of the modes, reported as LAYERED. */
+ * and the forward of large spaces of 6 to 8 photons, every sample alike,
+ * from two halves of the modes, reported as LAYERED. */
 #define SLOS_VARIANT_AUTO 0    /* library heuristic (or the last value set) */
 #define SLOS_VARIANT_FUSED 1   /* one persistent launch; each workgroup keeps a sample's photon layers in LDS */
 #define SLOS_VARIANT_LAYERED 2 /* one launch per photon layer; layers kept in the workspace (any size) */

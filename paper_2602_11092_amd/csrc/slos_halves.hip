@@ -3,15 +3,15 @@
 // matrix instructions.
 //
 // Layer by layer, every state of such a space is gathered from up to n states
-// far apart in a layer larger than the caches: m = 24, n = 8, 16 samples fetched
-// 4.4 GB for the last layer's 1 GB (1.15 ms of the forward's 1.50 ms).  The
-// halves' factors are 8.3 MB per half and sample, read in tiles; the cost is
-// arithmetic instead, 47 complex products per output at the FP32 matrix rate.  The same
-// forward now takes 0.81 ms: 0.58 ms of matrix products (25.5 million
+// far apart in a layer larger than the caches (m = 24, n = 8, 16 samples: the last
+// layer fetches about 4.4 GB for 0.5 GB of probabilities; 0.99 ms the forward).
+// The halves' factors are 8.3 MB per half and sample, read in tiles; the cost is
+// arithmetic instead, 47 complex products per output at the FP32 matrix rate.
+// The same forward takes 0.81 ms: 0.57 ms of matrix products (25.5 million
 // instructions, 0.40 ms at the measured 16 ns each per SIMD; vector
 // instructions do not overlap with FP32 matrix ones on a SIMD), 0.04 ms the
 // outputs with one photon in a half, 0.17 ms the factor tables.  Error of p
-// against 64 bits 2.2e-7 before, 1.7e-7 now (level sums in FP64, products in
+// against 64 bits 2.2e-7 by layers, 1.7e-7 here (level sums in FP64, products in
 // chains of at most 32).
 #include <type_traits>
 
@@ -349,7 +349,6 @@ int halves_tables(const HalvesDev& H, const BatchDev& dev, int nb, int m, const 
     hipError_t e = hipLaunchKernel((void*)&halves_columns_kernel, dim3((unsigned)nb), dim3(kBuildBlock), args, 0, stream);
     if (e != hipSuccess) return fail(SLOS_EHIP, std::string("two-halves launch: ") + hipGetErrorString(e));
     switch (H.n) {
-        case 5: return halves_levels<5, 2>(H, dev, nb, T, out, probs, stream);
         case 6: return halves_levels<6, 2>(H, dev, nb, T, out, probs, stream);
         case 7: return halves_levels<7, 2>(H, dev, nb, T, out, probs, stream);
         default: return halves_levels<8, 2>(H, dev, nb, T, out, probs, stream);
@@ -364,19 +363,22 @@ int halves_ntiles(const HalvesDev& H) {
 
 }  // namespace
 
-// Every sample the same photon number, and outputs enough to pay for the n + 2
-// launches and their tables.  Both sides measured, us, layer by layer against
-// two halves: n = 5, m = 25 (118755 outputs) B = 9 43 / 30, B = 3 20 / 28; n = 6,
-// m = 20 (177100) B = 64 264 / 84, B = 6 39 / 36, B = 2 23 / 35; n = 7, m = 14
-// (77520) B = 27 73 / 61, B = 16 46 / 53; m = 18 (346104) B = 6 59 / 55; n = 8,
-// m = 12 (75582) B = 64 164 / 113, B = 28 79 / 83; m = 24 (7888725) B = 1 146 / 103,
-// B = 16 1508 / 811.
+// Every sample the same photon number, a space large enough that layers miss the
+// caches, and outputs enough to pay for the n + 2 launches and their tables.
+// Both sides measured, us, layer by layer against two halves.  n = 8: m = 22 (4.3
+// million states) 4 samples 167 / 166, m = 23 (5.9) 1 sample 104 / 91, m = 24
+// (7.9) 1 sample 135 / 101, 16 samples 995 / 812, m = 28 (23.5) 1 sample 340 / 184.  n = 7:
+// m = 20 (0.66) 32 samples 152 / 159, m = 24 (2.0) 8 samples 118 / 121, m = 26 (3.4)
+// 2 samples 69 / 75, 5 samples 192 / 121, m = 28 (5.4) 1 sample 83 / 64.  n = 6: m = 24
+// (0.48) 16 samples 70 / 66, m = 28 (1.1) 4 samples 49 / 48, 8 samples 69 / 65, 32
+// samples 207 / 159.  n = 5 gains 10 % at most (m = 32, 32 samples 81 / 73) and is
+// left to the layers.
 bool halves_ok(const slos_batch_s& Bt) {
     if (Bt.B < 1 || Bt.n_min != Bt.n_max || Bt.n_max > kHalvesMaxN) return false;
     const HalvesDev& H = Bt.plan->halves[Bt.n_max];
-    if (H.n == 0 || Bt.plan->N[H.n] > kHalvesMaxStates) return false;
-    const int64_t least = H.n <= 6 ? 1000000 : H.n == 7 ? 2000000 : 3000000;
-    return Bt.plan->N[H.n] * Bt.B >= least;
+    const int64_t N = Bt.plan->N[Bt.n_max];
+    if (H.n == 0 || N > kHalvesMaxStates) return false;
+    return N >= 5000000 || N * Bt.B >= (H.n == 6 ? 8000000 : 16000000);
 }
 
 // Samples per pass: equal passes whose factor tables stay below kHalvesWsBytes.
@@ -396,8 +398,7 @@ int launch_halves_fwd(const slos_batch_s& Bt, const float2* U, void* out, bool p
     const int pass = halves_pass(Bt), m = Bt.plan->m;
     const int rows = std::max(H.D[0][H.n - 1], H.D[1][H.n - 1]);
     int ntiles = halves_ntiles(H);
-    void* edge = H.n == 5   ? (probs ? (void*)&halves_edge_kernel<5, true> : (void*)&halves_edge_kernel<5, false>)
-                 : H.n == 6 ? (probs ? (void*)&halves_edge_kernel<6, true> : (void*)&halves_edge_kernel<6, false>)
+    void* edge = H.n == 6   ? (probs ? (void*)&halves_edge_kernel<6, true> : (void*)&halves_edge_kernel<6, false>)
                  : H.n == 7 ? (probs ? (void*)&halves_edge_kernel<7, true> : (void*)&halves_edge_kernel<7, false>)
                             : (probs ? (void*)&halves_edge_kernel<8, true> : (void*)&halves_edge_kernel<8, false>);
     void* tile = probs ? (void*)&halves_fwd_kernel<true> : (void*)&halves_fwd_kernel<false>;

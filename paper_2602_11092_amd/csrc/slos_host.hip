@@ -538,12 +538,12 @@ extern "C" int slos_plan_create(int m, int n_max, int flags, slos_plan_t* out) {
         o_tpr[k] = total;  total += align256(H[k].thr_pred.size() * 4);
         o_tnr[k] = total;  total += align256(H[k].thr_nrm.size() * 4);
     }
-    // the two-halves tables of the photon numbers whose layers the on-chip
-    // kernels cannot hold (4 bytes per low-half state of each level)
+    // the two-halves tables of the photon numbers that may take them (4 bytes
+    // per low-half state of each level)
     std::vector<int32_t> HB[kHalvesMaxN + 1], HM[kHalvesMaxN + 1];
     size_t o_hb[kHalvesMaxN + 1] = {}, o_hm[kHalvesMaxN + 1] = {};
     for (int n = kHalvesMinN; n <= std::min(n_max, kHalvesMaxN); ++n) {
-        if (group != 0 || m < 4 || P->N[n] < (n == 5 ? 100000 : 20000)) continue;
+        if (group != 0 || P->N[n] < halves_min_states(n)) continue;
         build_halves(m, n, P->halves[n], HB[n], HM[n]);
         o_hb[n] = total; total += align256(HB[n].size() * 4);
         o_hm[n] = total; total += align256(HM[n].size() * 4);

@@ -5,17 +5,40 @@
 //
 // Same recursion as the fused kernels (arXiv 2602.11092, Sec. II-A-3):
 // layer k is pulled from layer k-1 through the transition tables.  The
-// batch is split into groups of SG samples (SG a power of two <= 64) and
-// each layer is stored [group][state][SG], so the SG lanes that share a
+// batch is split into groups of SG samples (SG a power of two <= 8) and
+// each layer is stored [group][state][SG], so the lanes that share a
 // state read one contiguous SG*8-byte segment per gather.  The backward
 // recomputes layers 1..n-1 into the workspace, then walks k = n..1 with a
 // seed launch (top-layer gradient of the samples whose top is layer k), a
 // pull launch (g_{k-1} and the partial sums of G_U[:, i_k]) and, at the
 // end, one launch that adds the partial sums in a fixed order.
+//
+// Bound by the gathers past the L2s: of a state's k neighbours the ones that
+// differ in an early photon are far away.  What that costs depends on how much
+// is in flight and how long a line stays, hence: lanes of two samples (16-byte
+// loads; half the addresses, table entries and instructions), a state's gathers
+// issued together with the next state's table entries behind them, groups of
+// 8 samples (64-byte segments; with 64 samples a group the same window of states
+// is eight times the bytes), one contiguous eighth of the states per XCD, and a
+// grid that is resident at once.  Forward and adjoint, us, before -> now: m = 24,
+// n = 8, 16 samples 1502 -> 995, 2766 -> 2175 (5 TB/s past the L2s, the rate a large
+// copy has); m = 20, n = 6, 64 samples 265 -> 92, 469 -> 208; m = 14, n = 7, 64
+// samples 152 -> 68, 306 -> 160; m = 24, n = 8, 1 sample 145 -> 135, 469 -> 333.
 #include "slos_internal.h"
 
 namespace slos {
 namespace {
+
+// Blocks of a pull launch along the states, over all groups about two grids of
+// four per CU (its registers allow 4 waves per SIMD): m = 24, n = 8, 16 samples
+// 2175 us with 1024, 2327 with 768 and 2339 with 2048.  A layer launch keeps about 5
+// per CU: m = 20, n = 6, 512 samples 1321 us with 2560 over all groups, 1643 with 2048
+// for each group.
+constexpr int kPullBlocks = 1024, kLayerBlocks = 2560;
+// The lanes of a state share its successors, a part of the modes each: 2 parts for
+// lanes of two samples (4: m = 24, n = 8, 16 samples 2398 us against 2175), 4 for a
+// lone sample (1, 2, 4, 8 parts: 624, 370, 333, 361 us).
+constexpr int kParts1 = 4, kParts2 = 2;
 
 struct Shape {
     int SG;    // samples per group (lanes sharing a state)
@@ -23,17 +46,28 @@ struct Shape {
     int GX;    // blocks along the state axis in the pull launches
 };
 
+// Groups of 8 samples: m = 20, n = 6, 64 samples 272 us with 8, 277 with 16, 344
+// with 64, 294 with 4; m = 28, n = 5, 40 samples 222, 241, 316, 250.  (64 for batches whose
+// groups of 8 would not fit the grid.)
 Shape shape_of(const slos_batch_s& Bt) {
+    const int most = Bt.B <= 8 * 32768 ? 8 : 64;
     int sg = 1;
-    while (sg < Bt.B && sg < 64) sg <<= 1;
+    while (sg < Bt.B && sg < most) sg <<= 1;
     const int ngrp = (Bt.B + sg - 1) / sg;
-    // no more blocks than the largest pull range needs (256 threads each); with
-    // one group, 1024 blocks (four per CU, what the pull's LDS allows) keep 4
-    // waves per SIMD waiting on the gathers
+    // no more blocks than the largest pull range needs (256 threads each)
     const int64_t Nmax = Bt.n_max >= 1 ? Bt.plan->N[Bt.n_max - 1] : 1;
-    const int64_t need = (Nmax * sg + 255) / 256;
-    const int cap = std::max(8, std::min(1024, 2048 / ngrp));
-    return Shape{sg, ngrp, (int)std::max<int64_t>(1, std::min<int64_t>(need, cap))};
+    const int64_t need = (Nmax * sg + 255) / 256 * (sg > 1 ? 1 : kParts1);
+    const int cap = std::max(8, std::min(kPullBlocks, 2 * kPullBlocks / ngrp));
+    int gx = (int)std::max<int64_t>(1, std::min<int64_t>(need, cap));
+    if (gx >= 64) gx &= ~7;
+    return Shape{sg, ngrp, gx};
+}
+
+// Blocks of a pull over Nprev states: no more than have work.
+__host__ __device__ __forceinline__ int pull_blocks(int64_t Nprev, int SG, int GX) {
+    const int64_t need = (Nprev * (SG > 1 ? SG / 2 * kParts2 : kParts1) + 255) / 256;
+    const int gx = need < GX ? (int)need : GX;
+    return gx >= 64 ? gx & ~7 : gx;
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -75,110 +109,209 @@ Layout layout_of(const slos_batch_s& Bt, bool backward) {
     return L;
 }
 
+// A block's states of [0, N): workgroups are dealt to the eight XCDs in turn, so
+// with a grid of a multiple of eight each XCD is given one contiguous eighth.
+struct Range {
+    int t, end, step;
+};
+__device__ __forceinline__ Range block_range(int N, int TPB, int tl) {
+    const int xcds = gridDim.x % 8 == 0 ? 8 : 1;
+    const int seg = (N + xcds - 1) / xcds, lo = (int)(blockIdx.x % xcds) * seg;
+    return Range{lo + (int)(blockIdx.x / xcds) * TPB + tl, min(N, lo + seg), (int)(gridDim.x / xcds) * TPB};
+}
+
+
 enum Mode { kForward = 0, kRecompute = 1, kSeed = 2 };
+
+// V adjacent samples of one state.
+template <int V>
+struct Vec {
+    float2 s[V];
+};
+template <int V>
+__device__ __forceinline__ Vec<V> ld_vec(const float2* p) {
+    Vec<V> r;
+    if constexpr (V == 2) {
+        const float4 v = *(const float4*)p;
+        r.s[0] = make_float2(v.x, v.y);
+        r.s[1] = make_float2(v.z, v.w);
+    } else {
+        r.s[0] = *p;
+    }
+    return r;
+}
+
+template <int V>
+__device__ __forceinline__ void st_vec(float2* p, const Vec<V>& x, const bool (&on)[V], bool all) {
+    if (V == 2 && all) {
+        *(float4*)p = make_float4(x.s[0].x, x.s[0].y, x.s[V - 1].x, x.s[V - 1].y);
+    } else {
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (on[v]) p[v] = x.s[v];
+    }
+}
 
 // One layer for every active sample of a group.  kForward: samples whose top
 // layer is k write their outputs, the others write layer k.  kRecompute:
 // only samples with more than k photons, writing layer k.  kSeed: only
-// samples whose top layer is k, writing g_k.
-template <int BLOCK, bool PROBS>
+// samples whose top layer is k, writing g_k.  A lane takes V samples (2 when the
+// group has as many), one 16-byte load each for the state and the coefficient.
+template <int BLOCK, bool PROBS, int V>
 __global__ __launch_bounds__(BLOCK) void layered_layer_kernel(int m, const LayerDev* __restrict__ Ls, BatchDev Bt,
                                                               const float2* __restrict__ U, int k, int mode,
                                                               const float2* __restrict__ prev, float2* __restrict__ cur,
                                                               void* __restrict__ out, const void* __restrict__ gin,
                                                               int SG) {
-    __shared__ float2 us[64 * kUcolSlots];
+    __shared__ __attribute__((aligned(16))) float2 us[64 * kUcolSlots];  // [slot][SG]
     const int tid = threadIdx.x;
-    const int bl = tid % SG;
-    const int tl = tid / SG;
-    const int TPB = BLOCK / SG;
+    const int per = SG / V;  // lanes of one state
+    const int bl = tid % per * V;
+    const int tl = tid / per;
+    const int TPB = BLOCK / per;
     const int g = blockIdx.y;
-    const int b = g * SG + bl;
-    const int n_b = (b < Bt.B) ? Bt.n[b] : -1;
-    const bool active = (mode == kForward) ? n_b >= k : (mode == kRecompute) ? n_b > k : n_b == k;
+    bool active[V], top[V], any = false, all = true;
+    float innorm[V];
+    int64_t off[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int b = g * SG + bl + v;
+        const int n_b = b < Bt.B ? Bt.n[b] : -1;
+        active[v] = mode == kForward ? n_b >= k : mode == kRecompute ? n_b > k : n_b == k;
+        top[v] = n_b == k;
+        any |= active[v];
+        all &= active[v];
+        innorm[v] = active[v] ? Bt.innorm[b] : 0.f;
+        off[v] = active[v] ? Bt.off[b] : 0;
+    }
     // stage column i_k of U for every sample of the group (slot 32 = 0)
-    for (int q = tid; q < SG; q += BLOCK) us[q * kUcolSlots + 32] = c_zero();
+    for (int q = tid; q < SG; q += BLOCK) us[32 * SG + q] = c_zero();
     for (int q = tid; q < SG * m; q += BLOCK) {
         const int bq = q % SG, j = q / SG;
         const int bb = g * SG + bq;
         if (bb < Bt.B && Bt.n[bb] >= k) {
             const int ik = Bt.modes[(size_t)bb * kMaxPhotons + k - 1];
-            us[bq * kUcolSlots + j] = U[((size_t)bb * m + j) * m + ik];
+            us[j * SG + bq] = U[((size_t)bb * m + j) * m + ik];
         }
     }
     __syncthreads();
-    if (!active) return;
+    if (!any) return;
     const LayerDev L = Ls[k];
     const int N = (int)L.N;
     const int Nprev = (int)Ls[k - 1].N;
-    const bool top = (n_b == k);
-    const float innorm = Bt.innorm[b];
-    const int64_t off = Bt.off[b];
-    for (int t = blockIdx.x * TPB + tl; t < N; t += gridDim.x * TPB) {
-        float2 acc = c_zero();
-        const bool need_d = !(mode == kSeed && !PROBS);
-        if (need_d) {
-            if (k == 1) {
-                acc = us[bl * kUcolSlots + t];
-            } else {
-                const int sh = L.pred_shift;
-                const uint32_t rmask = pred_rank_mask(sh);
-                for (int gq = 0; gq < L.ngrp; ++gq) {
-                    const uint4 e4 = L.predv[(size_t)gq * N + t];
-                    const uint32_t es[4] = {e4.x, e4.y, e4.z, e4.w};
+    const int sh = L.pred_shift, ngrp = L.ngrp;
+    const uint32_t rmask = pred_rank_mask(sh);
+    const bool need_d = !(mode == kSeed && !PROBS), table = need_d && k > 1;
+    const float2* pg = prev + (size_t)g * Nprev * SG + bl;
+    const Range R = block_range(N, TPB, tl);
+    uint4 e0 = {}, e1 = {};
+    if (table && R.t < R.end) {
+        e0 = L.predv[R.t];
+        if (ngrp > 1) e1 = L.predv[(size_t)N + R.t];
+    }
+    for (int t = R.t; t < R.end; t += R.step) {
+        Vec<V> acc;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        // empty entries name the zero slot 32 of the coefficient column
-                        const uint32_t e = es[q];
-                        c_fma(acc, us[bl * kUcolSlots + (e >> sh)],
-                              prev[((size_t)g * Nprev + ((e & rmask) >> 3)) * SG + bl]);
-                    }
+        for (int v = 0; v < V; ++v) acc.s[v] = c_zero();
+        if (table) {
+            // two groups' gathers in flight at once, and the next state's entries behind them
+            const uint4 c0 = e0, c1 = e1;
+            const uint32_t es[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+            Vec<V> d[8];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) d[q] = ld_vec<V>(pg + (size_t)((es[q] & rmask) >> 3) * SG);
+            if (ngrp > 1) {
+#pragma unroll
+                for (int q = 4; q < 8; ++q) d[q] = ld_vec<V>(pg + (size_t)((es[q] & rmask) >> 3) * SG);
+            }
+            const int tn = t + R.step < R.end ? t + R.step : t;
+            e0 = L.predv[tn];
+            if (ngrp > 1) e1 = L.predv[(size_t)N + tn];
+            // empty entries name the zero slot 32 of the coefficient column
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const Vec<V> u = ld_vec<V>(us + (es[q] >> sh) * SG + bl);
+#pragma unroll
+                for (int v = 0; v < V; ++v) c_fma(acc.s[v], u.s[v], d[q].s[v]);
+            }
+            if (ngrp > 1) {
+#pragma unroll
+                for (int q = 4; q < 8; ++q) {
+                    const Vec<V> u = ld_vec<V>(us + (es[q] >> sh) * SG + bl);
+#pragma unroll
+                    for (int v = 0; v < V; ++v) c_fma(acc.s[v], u.s[v], d[q].s[v]);
                 }
             }
+            for (int gq = 2; gq < ngrp; ++gq) {
+                const uint4 e4 = L.predv[(size_t)gq * N + t];
+                const uint32_t ex[4] = {e4.x, e4.y, e4.z, e4.w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const Vec<V> u = ld_vec<V>(us + (ex[q] >> sh) * SG + bl);
+                    const Vec<V> x = ld_vec<V>(pg + (size_t)((ex[q] & rmask) >> 3) * SG);
+#pragma unroll
+                    for (int v = 0; v < V; ++v) c_fma(acc.s[v], u.s[v], x.s[v]);
+                }
+            }
+        } else if (need_d) {
+            acc = ld_vec<V>(us + t * SG + bl);
         }
-        if (mode == kForward && top) {
-            const float c = L.nrm[t] * innorm;
-            if (PROBS) ((float*)out)[off + t] = c * c * (acc.x * acc.x + acc.y * acc.y);
-            else ((float2*)out)[off + t] = c_scale(acc, c);
-        } else if (mode == kSeed) {
-            const float c = L.nrm[t] * innorm;
-            float2 gv;
-            if (PROBS) gv = c_scale(acc, 2.f * ((const float*)gin)[off + t] * c * c);
-            else gv = c_scale(((const float2*)gin)[off + t], c);
-            cur[((size_t)g * N + t) * SG + bl] = gv;
-        } else {
-            cur[((size_t)g * N + t) * SG + bl] = acc;
+        float2* to = cur + ((size_t)g * N + t) * SG + bl;
+        bool store[V], both = all;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            store[v] = active[v];
+            if (!active[v]) continue;
+            if (mode == kForward && top[v]) {
+                const float c = L.nrm[t] * innorm[v];
+                const float2 a = acc.s[v];
+                if (PROBS) ((float*)out)[off[v] + t] = c * c * (a.x * a.x + a.y * a.y);
+                else ((float2*)out)[off[v] + t] = c_scale(a, c);
+                store[v] = both = false;
+            } else if (mode == kSeed) {
+                const float c = L.nrm[t] * innorm[v];
+                if (PROBS) acc.s[v] = c_scale(acc.s[v], 2.f * ((const float*)gin)[off[v] + t] * c * c);
+                else acc.s[v] = c_scale(((const float2*)gin)[off[v] + t], c);
+            }
         }
+        st_vec<V>(to, acc, store, both);
     }
 }
 
 // g_{k-1}[t'] = sum_j conj(u_j) g_k[t'+e_j]; partial sums of
-// G_U[j][i_k] = sum_t' conj(d_{k-1}[t']) g_k[t'+e_j] per block.  Each lane
-// keeps its G_U partials for MMAX modes in registers (modes past m read
-// padding successors and zero coefficients and are never written out),
-// loads the successors of four modes at once, and the block adds the lanes
-// of each sample in a fixed order through an LDS window of 8 modes.
+// G_U[j][i_k] = sum_t' conj(d_{k-1}[t']) g_k[t'+e_j] per block.  A lane takes V
+// samples and one of PARTS shares of the modes (MMAX in all), whose G_U partials
+// it keeps in registers (modes past m read padding successors and zero
+// coefficients and are never written out); the lanes of a state add their
+// shares of g_{k-1} across the wave, and the block adds the lanes of each
+// sample in a fixed order through LDS, four modes at a time.
 // RESTRICTED: plans of a restricted space, whose successor tables mark
 // successors outside the space with kNoSuccessor; those pairs contribute
 // nothing (the forward never formed such states).
-
-template <int BLOCK, int MMAX, bool RESTRICTED>
+template <int BLOCK, int MMAX, bool RESTRICTED, int V, int PARTS>
 __global__ __launch_bounds__(BLOCK) void layered_pull_kernel(int m, const LayerDev* __restrict__ Ls, BatchDev Bt,
                                                              const float2* __restrict__ U, int k,
                                                              const float2* __restrict__ gk, float2* __restrict__ gkm1,
                                                              const float2* __restrict__ dkm1,
-                                                             float2* __restrict__ partial, int SG, int NGRP) {
-    constexpr int WIN = 8;
-    __shared__ float2 us[64 * kUcolSlots];
-    __shared__ float2 Hs[WIN * BLOCK];
+                                                             float2* __restrict__ partial, int SG, int NGRP, int GX) {
+    constexpr int G = (MMAX / 4 + PARTS - 1) / PARTS;  // successor groups (of four modes) per lane
+    __shared__ __attribute__((aligned(16))) float2 lds[64 * kUcolSlots];
+    static_assert(4 * V * BLOCK <= 64 * kUcolSlots, "the lanes' sums reuse the column's memory");
+    float2* us = lds;  // [slot][SG]
     const int tid = threadIdx.x;
-    const int bl = tid % SG;
-    const int tl = tid / SG;
-    const int TPB = BLOCK / SG;
+    const int per = SG / V, lanes = per * PARTS;  // lanes of one state
+    const int bl = tid % per * V, part = tid / per % PARTS;  // samples bl .. bl+V-1, modes from 4 G part on
+    const int tl = tid / lanes;
+    const int TPB = BLOCK / lanes;
     const int g = blockIdx.y;
-    const int b = g * SG + bl;
-    const int n_b = (b < Bt.B) ? Bt.n[b] : -1;
-    const bool active = n_b >= k;
+    bool active[V], any = false, all = true;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int b = g * SG + bl + v;
+        active[v] = b < Bt.B && Bt.n[b] >= k;
+        any |= active[v];
+        all &= active[v];
+    }
     for (int q = tid; q < SG * kUcolSlots; q += BLOCK) us[q] = c_zero();
     __syncthreads();
     for (int q = tid; q < SG * m; q += BLOCK) {
@@ -186,62 +319,88 @@ __global__ __launch_bounds__(BLOCK) void layered_pull_kernel(int m, const LayerD
         const int bb = g * SG + bq;
         if (bb < Bt.B && Bt.n[bb] >= k) {
             const int ik = Bt.modes[(size_t)bb * kMaxPhotons + k - 1];
-            us[bq * kUcolSlots + j] = U[((size_t)bb * m + j) * m + ik];
+            us[j * SG + bq] = U[((size_t)bb * m + j) * m + ik];
         }
     }
     __syncthreads();
-    float2 h[MMAX];
+    Vec<V> h[4 * G];
 #pragma unroll
-    for (int j = 0; j < MMAX; ++j) h[j] = c_zero();
-    if (active) {
+    for (int j = 0; j < 4 * G; ++j)
+#pragma unroll
+        for (int v = 0; v < V; ++v) h[j].s[v] = c_zero();
+    if (any) {
         const int Nk = (int)Ls[k].N;
         const int Nkm1 = (int)Ls[k - 1].N;
-        const uint4* succ4 = (const uint4*)Ls[k].succ;
         const int ngs = (m + 3) >> 2;  // successor groups in the table
+        const uint4* succ4 = (const uint4*)Ls[k].succ + (size_t)min(G * part, ngs - 1) * Nkm1;
+        const int mine = ngs - G * part;  // this lane's groups
         const float2* gkg = gk + (size_t)g * Nk * SG + bl;
-        for (int tp = blockIdx.x * TPB + tl; tp < Nkm1; tp += gridDim.x * TPB) {
-            const float2 dv = (k >= 2) ? dkm1[((size_t)g * Nkm1 + tp) * SG + bl] : make_float2(1.f, 0.f);
-            float2 acc = c_zero();
+        const float2* ul = us + 4 * G * part * SG + bl;
+        const Range R = block_range(Nkm1, TPB, tl);
+        for (int tp = R.t; tp < R.end; tp += R.step) {
+            Vec<V> dv, acc;
 #pragma unroll
-            for (int q4 = 0; q4 < MMAX / 4; ++q4) {
-                if (q4 >= ngs) continue;  // uniform
-                const uint4 s4 = succ4[(size_t)q4 * Nkm1 + tp];
-                const uint32_t sv[4] = {s4.x, s4.y, s4.z, s4.w};
-                float2 gv[4];
+            for (int v = 0; v < V; ++v) {
+                dv.s[v] = make_float2(1.f, 0.f);
+                acc.s[v] = c_zero();
+            }
+            if (k >= 2) dv = ld_vec<V>(dkm1 + ((size_t)g * Nkm1 + tp) * SG + bl);
+            uint4 s4[G];
+#pragma unroll
+            for (int q4 = 0; q4 < G; ++q4) s4[q4] = succ4[(size_t)(q4 < mine ? q4 : 0) * Nkm1 + tp];
+#pragma unroll
+            for (int q4 = 0; q4 < G; ++q4) {
+                if (q4 >= mine) continue;
+                const uint32_t sv[4] = {s4[q4].x, s4[q4].y, s4[q4].z, s4[q4].w};
+                Vec<V> gv[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    if (RESTRICTED) {
-                        const bool none = sv[q] == kNoSuccessor;
-                        const float2 v = gkg[(size_t)((none ? 0u : sv[q]) >> 3) * SG];
-                        gv[q] = none ? c_zero() : v;
-                    } else {
-                        gv[q] = gkg[(size_t)(sv[q] >> 3) * SG];
+                    const bool none = RESTRICTED && sv[q] == kNoSuccessor;
+                    gv[q] = ld_vec<V>(gkg + (size_t)((none ? 0u : sv[q]) >> 3) * SG);
+#pragma unroll
+                    for (int v = 0; v < V; ++v)
+                        if (none) gv[q].s[v] = c_zero();
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const Vec<V> u = ld_vec<V>(ul + (4 * q4 + q) * SG);
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        c_fma_conj(acc.s[v], u.s[v], gv[q].s[v]);
+                        c_fma_conj(h[4 * q4 + q].s[v], dv.s[v], gv[q].s[v]);
                     }
                 }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    c_fma_conj(acc, us[bl * kUcolSlots + 4 * q4 + q], gv[q]);
-                    c_fma_conj(h[4 * q4 + q], dv, gv[q]);
-                }
             }
-            if (k >= 2) gkm1[((size_t)g * Nkm1 + tp) * SG + bl] = acc;
+            if (k >= 2) {
+                float2* to = gkm1 + ((size_t)g * Nkm1 + tp) * SG + bl;
+#pragma unroll
+                for (int x = 1; x < PARTS; x *= 2)
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        acc.s[v].x += __shfl_xor(acc.s[v].x, x * per);
+                        acc.s[v].y += __shfl_xor(acc.s[v].y, x * per);
+                    }
+                if (part == 0) st_vec<V>(to, acc, active, all);
+            }
         }
     }
-    // fixed-order sum over the lanes that share a sample, WIN modes at a time
+    // fixed-order sum over the lanes that share a sample, one group at a time
 #pragma unroll
-    for (int j0 = 0; j0 < MMAX; j0 += WIN) {
+    for (int q4 = 0; q4 < G; ++q4) {
         __syncthreads();
 #pragma unroll
-        for (int w = 0; w < WIN; ++w)
-            if (j0 + w < MMAX) Hs[w * BLOCK + tid] = h[j0 + w];
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int v = 0; v < V; ++v) lds[(V * q + v) * BLOCK + tid] = h[4 * q4 + q].s[v];
         __syncthreads();
-        for (int q = tid; q < SG * WIN; q += BLOCK) {
-            const int bq = q % SG, w = q / SG;
-            const int j = j0 + w;
+        for (int e = tid; e < SG * PARTS * 4; e += BLOCK) {
+            const int s = e % SG, pt = e / SG % PARTS, q = e / SG / PARTS;
+            const int j = 4 * (G * pt + q4) + q;
             if (j >= 32) continue;
+            const float2* src = lds + (V * q + s % V) * BLOCK + pt * per + s / V;
             float2 sum = c_zero();
-            for (int tq = 0; tq < TPB; ++tq) sum = c_add(sum, Hs[w * BLOCK + tq * SG + bq]);
-            partial[((((size_t)(k - 1) * NGRP + g) * gridDim.x + blockIdx.x) * SG + bq) * 32 + j] = sum;
+            for (int tq = 0; tq < TPB; ++tq) sum = c_add(sum, src[tq * lanes]);
+            partial[((((size_t)(k - 1) * NGRP + g) * GX + blockIdx.x) * SG + s) * 32 + j] = sum;
         }
     }
 }
@@ -251,7 +410,8 @@ __global__ __launch_bounds__(BLOCK) void layered_pull_kernel(int m, const LayerD
 // every 32nd block partial with eight independent accumulators, then the
 // slices are added in order.  The order is fixed, so results are
 // reproducible; the loads of a slice are all independent.
-__global__ __launch_bounds__(1024) void layered_reduce_kernel(BatchDev Bt, const float2* __restrict__ partial,
+__global__ __launch_bounds__(1024) void layered_reduce_kernel(const LayerDev* __restrict__ Ls, BatchDev Bt,
+                                                              const float2* __restrict__ partial,
                                                               float2* __restrict__ col, int SG, int NGRP, int GX) {
     __shared__ float2 part[32][33];
     const int b = blockIdx.x;
@@ -264,12 +424,13 @@ __global__ __launch_bounds__(1024) void layered_reduce_kernel(BatchDev Bt, const
     float2 a[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) a[q] = c_zero();
+    const int nx = pull_blocks(Ls[k - 1].N, SG, GX);
     int x = sl;
-    for (; x + 7 * 32 < GX; x += 8 * 32) {
+    for (; x + 7 * 32 < nx; x += 8 * 32) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) a[q] = c_add(a[q], src[(size_t)(x + q * 32) * xs]);
     }
-    for (; x < GX; x += 32) a[0] = c_add(a[0], src[(size_t)x * xs]);
+    for (; x < nx; x += 32) a[0] = c_add(a[0], src[(size_t)x * xs]);
     float2 v = c_zero();
 #pragma unroll
     for (int q = 0; q < 8; ++q) v = c_add(v, a[q]);
@@ -306,14 +467,14 @@ __global__ void vacuum_kernel(BatchDev Bt, void* out, int probs) {
     else ((float2*)out)[Bt.off[b]] = make_float2(1.f, 0.f);
 }
 
-template <bool PROBS>
+template <bool PROBS, int V>
 void* layer_fn(int block) {
     switch (block) {
-        case 64: return (void*)&layered_layer_kernel<64, PROBS>;
-        case 128: return (void*)&layered_layer_kernel<128, PROBS>;
-        case 256: return (void*)&layered_layer_kernel<256, PROBS>;
-        case 512: return (void*)&layered_layer_kernel<512, PROBS>;
-        case 1024: return (void*)&layered_layer_kernel<1024, PROBS>;
+        case 64: return (void*)&layered_layer_kernel<64, PROBS, V>;
+        case 128: return (void*)&layered_layer_kernel<128, PROBS, V>;
+        case 256: return (void*)&layered_layer_kernel<256, PROBS, V>;
+        case 512: return (void*)&layered_layer_kernel<512, PROBS, V>;
+        case 1024: return (void*)&layered_layer_kernel<1024, PROBS, V>;
     }
     return nullptr;
 }
@@ -323,11 +484,14 @@ int launch_layer(const slos_batch_s& Bt, int block, const float2* U, int k, int 
     const slos_plan_s& P = *Bt.plan;
     const Shape sh = shape_of(Bt);
     if (block < sh.SG) block = sh.SG;
-    void* fn = probs ? layer_fn<true>(block) : layer_fn<false>(block);
+    const int V = sh.SG > 1 ? 2 : 1;
+    void* fn = V == 2 ? (probs ? layer_fn<true, 2>(block) : layer_fn<false, 2>(block))
+                      : (probs ? layer_fn<true, 1>(block) : layer_fn<false, 1>(block));
     if (!fn) return fail(SLOS_EUNSUPPORTED, "layered: bad block size");
-    const int TPB = block / sh.SG;
+    const int TPB = block / (sh.SG / V);
     const int64_t N = P.N[k];
-    const int gx = (int)std::max<int64_t>(1, std::min<int64_t>((N + TPB - 1) / TPB, 8192));
+    int gx = (int)std::max<int64_t>(1, std::min<int64_t>((N + TPB - 1) / TPB, std::max(8, std::min(1280, kLayerBlocks / sh.NGRP))));
+    if (gx >= 64) gx &= ~7;
     int m = P.m;
     const LayerDev* Ls = P.d_layers;
     int SG = sh.SG;
@@ -372,17 +536,20 @@ int launch_layered_fwd(const slos_batch_s& Bt, int block, const float2* U, void*
     return SLOS_OK;
 }
 
-template <bool R>
+template <bool R, int V, int PARTS>
 static void* pull_fn_r(int m) {
-    if (m <= 8) return (void*)&layered_pull_kernel<256, 8, R>;
-    if (m <= 12) return (void*)&layered_pull_kernel<256, 12, R>;
-    if (m <= 16) return (void*)&layered_pull_kernel<256, 16, R>;
-    if (m <= 20) return (void*)&layered_pull_kernel<256, 20, R>;
-    if (m <= 24) return (void*)&layered_pull_kernel<256, 24, R>;
-    return (void*)&layered_pull_kernel<256, 32, R>;
+    if (m <= 8) return (void*)&layered_pull_kernel<256, 8, R, V, PARTS>;
+    if (m <= 12) return (void*)&layered_pull_kernel<256, 12, R, V, PARTS>;
+    if (m <= 16) return (void*)&layered_pull_kernel<256, 16, R, V, PARTS>;
+    if (m <= 20) return (void*)&layered_pull_kernel<256, 20, R, V, PARTS>;
+    if (m <= 24) return (void*)&layered_pull_kernel<256, 24, R, V, PARTS>;
+    return (void*)&layered_pull_kernel<256, 32, R, V, PARTS>;
 }
 
-static void* pull_fn(int m, bool restricted) { return restricted ? pull_fn_r<true>(m) : pull_fn_r<false>(m); }
+static void* pull_fn(int m, bool restricted, int V) {
+    if (V == 2) return restricted ? pull_fn_r<true, 2, kParts2>(m) : pull_fn_r<false, 2, kParts2>(m);
+    return restricted ? pull_fn_r<true, 1, kParts1>(m) : pull_fn_r<false, 1, kParts1>(m);
+}
 
 int launch_layered_bwd(const slos_batch_s& Bt, int block, const float2* U, const void* gin, bool probs, float2* gU,
                        void* ws, hipStream_t stream) {
@@ -400,7 +567,7 @@ int launch_layered_bwd(const slos_batch_s& Bt, int block, const float2* U, const
     }
     int m = P.m;
     const LayerDev* Ls = P.d_layers;
-    int SG = sh.SG, NGRP = sh.NGRP;
+    int SG = sh.SG, NGRP = sh.NGRP, GX = sh.GX;
     for (int k = Bt.n_max; k >= 1; --k) {
         float2* gk = gbuf[(Bt.n_max - k) & 1];
         float2* gkm1 = gbuf[(Bt.n_max - k + 1) & 1];
@@ -414,15 +581,14 @@ int launch_layered_bwd(const slos_batch_s& Bt, int block, const float2* U, const
         }
         const float2* dkm1 = store(k - 1);
         void* args[] = {(void*)&m, (void*)&Ls, (void*)&Bt.dev, (void*)&U, (void*)&k, (void*)&gk,
-                        (void*)&gkm1, (void*)&dkm1, (void*)&partial, (void*)&SG, (void*)&NGRP};
+                        (void*)&gkm1, (void*)&dkm1, (void*)&partial, (void*)&SG, (void*)&NGRP, (void*)&GX};
         const bool restricted = (P.flags & (SLOS_PLAN_UNBUNCHED | SLOS_PLAN_DUAL_RAIL)) != 0;
-        hipError_t e = hipLaunchKernel(pull_fn(m, restricted), dim3(sh.GX, NGRP), dim3(256), args, 0, stream);
+        hipError_t e = hipLaunchKernel(pull_fn(m, restricted, SG > 1 ? 2 : 1), dim3(pull_blocks(P.N[k - 1], SG, GX), NGRP), dim3(256), args, 0, stream);
         if (e != hipSuccess) return fail(SLOS_EHIP, std::string("layered pull launch: ") + hipGetErrorString(e));
     }
-    int GX = sh.GX;
     float2* col = (float2*)(base + L.col);
     {
-        void* args[] = {(void*)&Bt.dev, (void*)&partial, (void*)&col, (void*)&SG, (void*)&NGRP, (void*)&GX};
+        void* args[] = {(void*)&Ls, (void*)&Bt.dev, (void*)&partial, (void*)&col, (void*)&SG, (void*)&NGRP, (void*)&GX};
         hipError_t e = hipLaunchKernel((void*)&layered_reduce_kernel, dim3(Bt.B, std::max(Bt.n_max, 1)), dim3(1024), args, 0, stream);
         if (e != hipSuccess) return fail(SLOS_EHIP, std::string("layered reduce launch: ") + hipGetErrorString(e));
     }
