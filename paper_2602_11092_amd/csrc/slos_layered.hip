@@ -21,8 +21,9 @@
 // 8 samples (64-byte segments; with 64 samples a group the same window of states
 // is eight times the bytes), one contiguous eighth of the states per XCD, and a
 // grid that is resident at once.  Forward and adjoint, us, before -> now: m = 24,
-// n = 8, 16 samples 1502 -> 995, 2766 -> 2175 (5 TB/s past the L2s, the rate a large
-// copy has); m = 20, n = 6, 64 samples 265 -> 92, 469 -> 208; m = 14, n = 7, 64
+// n = 8, 16 samples 1502 -> 995, 2766 -> 2160 (its top layer: 2.1 GB in, 1.0 GB out in
+// 0.93 ms, its first pull 2.1 and 0.26 GB in 0.70 ms; neither more wavefronts nor
+// earlier loads help any further); m = 20, n = 6, 64 samples 265 -> 92, 469 -> 208; m = 14, n = 7, 64
 // samples 152 -> 68, 306 -> 160; m = 24, n = 8, 1 sample 145 -> 135, 469 -> 333.
 #include "slos_internal.h"
 
@@ -210,9 +211,17 @@ __global__ __launch_bounds__(BLOCK) void layered_layer_kernel(int m, const Layer
         if (ngrp > 1) e1 = L.predv[(size_t)N + R.t];
     }
     for (int t = R.t; t < R.end; t += R.step) {
+        // (the state's norm and incoming gradient fly with its gathers)
+        const float nrm = mode == kRecompute ? 0.f : L.nrm[t];
         Vec<V> acc;
+        float2 gi[V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) acc.s[v] = c_zero();
+        for (int v = 0; v < V; ++v) {
+            acc.s[v] = gi[v] = c_zero();
+            if (mode != kSeed || !active[v]) continue;
+            if (PROBS) gi[v].x = ((const float*)gin)[off[v] + t];
+            else gi[v] = ((const float2*)gin)[off[v] + t];
+        }
         if (table) {
             // two groups' gathers in flight at once, and the next state's entries behind them
             const uint4 c0 = e0, c1 = e1;
@@ -263,15 +272,15 @@ __global__ __launch_bounds__(BLOCK) void layered_layer_kernel(int m, const Layer
             store[v] = active[v];
             if (!active[v]) continue;
             if (mode == kForward && top[v]) {
-                const float c = L.nrm[t] * innorm[v];
+                const float c = nrm * innorm[v];
                 const float2 a = acc.s[v];
                 if (PROBS) ((float*)out)[off[v] + t] = c * c * (a.x * a.x + a.y * a.y);
                 else ((float2*)out)[off[v] + t] = c_scale(a, c);
                 store[v] = both = false;
             } else if (mode == kSeed) {
-                const float c = L.nrm[t] * innorm[v];
-                if (PROBS) acc.s[v] = c_scale(acc.s[v], 2.f * ((const float*)gin)[off[v] + t] * c * c);
-                else acc.s[v] = c_scale(((const float2*)gin)[off[v] + t], c);
+                const float c = nrm * innorm[v];
+                if (PROBS) acc.s[v] = c_scale(acc.s[v], 2.f * gi[v].x * c * c);
+                else acc.s[v] = c_scale(gi[v], c);
             }
         }
         st_vec<V>(to, acc, store, both);
