@@ -737,7 +737,11 @@ __device__ __forceinline__ void reduce_columns(const float2 (&h)[MMAX], int m, u
 
 // RS: plans of a restricted space (unbunched, dual-rail), whose successor
 // tables mark successors outside the space; those pairs read the zero slot.
-template <int BLOCK, int OWN, int MMAX, bool RS>
+// CLICKS (with PROBS): gin holds dL/dP per click pattern, read through the states'
+// patterns; m = 20, n = 5, 512 samples: expanding them into memory first was a 30 us
+// launch of its own and 87 MB to read back.  Instances of their own: as a
+// run-time case it cost the other adjoints 2 % (175 -> 179 us).
+template <int BLOCK, int OWN, int MMAX, bool RS, bool CLICKS = false>
 __global__ __launch_bounds__(BLOCK) void fused_bwd_kernel(int m, const LayerDev* __restrict__ Ls, BatchDev Bt,
                                                           const float2* __restrict__ U,
                                                           const void* __restrict__ gin,
@@ -801,8 +805,9 @@ __global__ __launch_bounds__(BLOCK) void fused_bwd_kernel(int m, const LayerDev*
                 // hold registers through the whole kernel)
                 const int j = fresh_v(tid);
                 const float c = ldg(layer(Ls, 1).nrm + j) * innorm;
-                const float2 v = PROBS ? c_scale(lds_ld(Ust + 8u * (uint32_t)(j * m + mode_of(0))), 2.f * ((const float*)gin)[off + j] * c * c)
-                                       : c_scale(((const float2*)gin)[off + j], c);
+                const int64_t at = CLICKS ? ldc(Bt.thr_off + b) + ldg(ldc(&Ls[1].thr_pat) + j) : off + j;
+                const float2 v = PROBS ? c_scale(lds_ld(Ust + 8u * (uint32_t)(j * m + mode_of(0))), 2.f * ((const float*)gin)[at] * c * c)
+                                       : c_scale(((const float2*)gin)[at], c);
                 lds_st(GUacc + 8u * j, v);
             }
             __syncthreads();
@@ -838,8 +843,11 @@ __global__ __launch_bounds__(BLOCK) void fused_bwd_kernel(int m, const LayerDev*
             const __amdgpu_buffer_rsrc_t rs = buf_rsrc(Ln.succ, (uint32_t)((m + 3) / 4) * gstride);
             const __amdgpu_buffer_rsrc_t rn = buf_rsrc(Ln.nrm, (uint32_t)Ln.N * 4u);
             const __amdgpu_buffer_rsrc_t rg =
-                buf_rsrc(PROBS ? (const void*)((const float*)gin + off) : (const void*)((const float2*)gin + off),
-                         (uint32_t)Ln.N * (PROBS ? 4u : 8u));
+                CLICKS ? buf_rsrc((const float*)gin + ldc(Bt.thr_off + b),
+                                  (uint32_t)(ldc(Bt.thr_off + b + 1) - ldc(Bt.thr_off + b)) * 4u)
+                       : buf_rsrc(PROBS ? (const void*)((const float*)gin + off) : (const void*)((const float2*)gin + off),
+                                  (uint32_t)Ln.N * (PROBS ? 4u : 8u));
+            const __amdgpu_buffer_rsrc_t rp = CLICKS ? buf_rsrc(ldc(&Ls[n].thr_pat), (uint32_t)Ln.N * 4u) : rg;
             float2 acc[OWN];
             float2 h[MMAX];
 #pragma unroll
@@ -854,16 +862,21 @@ __global__ __launch_bounds__(BLOCK) void fused_bwd_kernel(int m, const LayerDev*
                 while (bb < m && minoff_n(bb + 1) - base <= cap) ++bb;
                 const int end = minoff_n(bb);
                 // g_n on the chunk: 2 dL/dp_t c_t^2 d_n[t] (probabilities; the
-                // factor loads issue together with the gather's table loads) or
-                // c_t G_a[t] (amplitudes, a streaming pass).
-                if (PROBS) {
+                // factor loads issue together with the gather's table loads; dL/dp_t
+                // of click patterns is dL/dP at the state's pattern) or c_t G_a[t]
+                // (amplitudes, a streaming pass).
+                if (CLICKS || PROBS) {
                     for (int t0 = base + tid; t0 < end; t0 += BLOCK * GM) {
                         float cv[GM], gv[GM];
 #pragma unroll
                         for (int q = 0; q < GM; ++q) {
                             const uint32_t tc = (uint32_t)min(t0 + q * BLOCK, end - 1);
                             cv[q] = buf_ldf(rn, tc * 4u, 0) * innorm;
-                            gv[q] = buf_ldf_stream(rg, tc * 4u);
+                            gv[q] = CLICKS ? buf_ldf(rp, tc * 4u, 0) : buf_ldf_stream(rg, tc * 4u);
+                        }
+                        if (CLICKS) {
+#pragma unroll
+                            for (int q = 0; q < GM; ++q) gv[q] = buf_ldf(rg, __float_as_uint(gv[q]) * 4u, 0);
                         }
                         float2 d[GM];
                         gather_states<BLOCK, GM, kLP, 2>(Ln, n, t0, end, D, d);
@@ -997,28 +1010,61 @@ int own_for(int block, int64_t Np) {
 
 int mmax_for(int m) { return m <= 8 ? 8 : m <= 12 ? 12 : m <= 16 ? 16 : m <= 20 ? 20 : m <= 24 ? 24 : 32; }
 
-template <int BLOCK, int OWN, bool R>
+template <int BLOCK, int OWN, bool R, bool C = false>
 void* bwd_by_m(int mm) {
     if constexpr (BLOCK >= 768) {
         if (mm > 20) return nullptr;  // h and acc do not fit the registers of 12 or 16 waves
     }
     switch (mm) {
-        case 8: return (void*)&fused_bwd_kernel<BLOCK, OWN, 8, R>;
-        case 12: return (void*)&fused_bwd_kernel<BLOCK, OWN, 12, R>;
-        case 16: return (void*)&fused_bwd_kernel<BLOCK, OWN, 16, R>;
-        case 20: return (void*)&fused_bwd_kernel<BLOCK, OWN, 20, R>;
+        case 8: return (void*)&fused_bwd_kernel<BLOCK, OWN, 8, R, C>;
+        case 12: return (void*)&fused_bwd_kernel<BLOCK, OWN, 12, R, C>;
+        case 16: return (void*)&fused_bwd_kernel<BLOCK, OWN, 16, R, C>;
+        case 20: return (void*)&fused_bwd_kernel<BLOCK, OWN, 20, R, C>;
         case 24:
-            if constexpr (BLOCK < 768) return (void*)&fused_bwd_kernel<BLOCK, OWN, 24, R>;
+            if constexpr (BLOCK < 768) return (void*)&fused_bwd_kernel<BLOCK, OWN, 24, R, C>;
             return nullptr;
         case 32:
             // h and acc do not fit the registers; no restricted instances at 32 modes
-            if constexpr (OWN <= 10 && BLOCK < 768 && !R) return (void*)&fused_bwd_kernel<BLOCK, OWN, 32, R>;
+            if constexpr (OWN <= 10 && BLOCK < 768 && !R) return (void*)&fused_bwd_kernel<BLOCK, OWN, 32, R, C>;
             return nullptr;
     }
     return nullptr;
 }
 
-#ifdef SLOS_FUSED_RESTRICTED_INSTANCES
+// instances for the full space
+template <bool C>
+void* pick_bwd_full(int block, int m, int64_t Np) {
+    const int own = own_for(block, Np);
+    const int mm = mmax_for(m);
+    if (block == 256) {
+        switch (own) {
+            case 1: return bwd_by_m<256, 1, false, C>(mm);
+            case 2: return bwd_by_m<256, 2, false, C>(mm);
+            case 4: return bwd_by_m<256, 4, false, C>(mm);
+        }
+    } else if (block == 512) {
+        switch (own) {
+            case 4: return bwd_by_m<512, 4, false, C>(mm);
+            case 10: return bwd_by_m<512, 10, false, C>(mm);
+            case 18: return bwd_by_m<512, 18, false, C>(mm);
+        }
+    } else if (block == 768) {
+        if (own == 12) return bwd_by_m<768, 12, false, C>(mm);
+    } else if (block == 1024) {
+        if (own == 10) return bwd_by_m<1024, 10, false, C>(mm);
+    }
+    return nullptr;
+}
+
+#if defined(SLOS_FUSED_CLICK_INSTANCES)
+}  // namespace
+
+// The adjoint instances that read click-pattern gradients; this translation
+// unit holds only them.
+void* pick_bwd_clicks(int block, int m, int64_t Np) { return pick_bwd_full<true>(block, m, Np); }
+
+}  // namespace slos
+#elif defined(SLOS_FUSED_RESTRICTED_INSTANCES)
 }  // namespace
 
 // The adjoint instances for restricted spaces (workgroups of 256 and 512,
@@ -1097,27 +1143,7 @@ size_t fwd_lds_for(const slos_plan_s& P, int n_max, int block, bool expect, bool
 }
 
 void* pick_bwd(int block, int m, int64_t Np, bool restricted) {
-    if (restricted) return pick_bwd_restricted(block, m, Np);
-    const int own = own_for(block, Np);
-    const int mm = mmax_for(m);
-    if (block == 256) {
-        switch (own) {
-            case 1: return bwd_by_m<256, 1, false>(mm);
-            case 2: return bwd_by_m<256, 2, false>(mm);
-            case 4: return bwd_by_m<256, 4, false>(mm);
-        }
-    } else if (block == 512) {
-        switch (own) {
-            case 4: return bwd_by_m<512, 4, false>(mm);
-            case 10: return bwd_by_m<512, 10, false>(mm);
-            case 18: return bwd_by_m<512, 18, false>(mm);
-        }
-    } else if (block == 768) {
-        if (own == 12) return bwd_by_m<768, 12, false>(mm);
-    } else if (block == 1024) {
-        if (own == 10) return bwd_by_m<1024, 10, false>(mm);
-    }
-    return nullptr;
+    return restricted ? pick_bwd_restricted(block, m, Np) : pick_bwd_full<false>(block, m, Np);
 }
 
 size_t bwd_lds_for_block(const slos_plan_s& P, int n_max, int block) {
@@ -1230,13 +1256,13 @@ int launch_fused_fwd(const slos_batch_s& Bt, int block, const float2* U, void* o
     return SLOS_OK;
 }
 
-int launch_fused_bwd(const slos_batch_s& Bt, int block, const float2* U, const void* gin, bool probs,
+int launch_fused_bwd(const slos_batch_s& Bt, int block, const float2* U, const void* gin, int kind,
                      float2* gU, hipStream_t stream) {
     const slos_plan_s& P = *Bt.plan;
     std::string why;
     if (!fused_bwd_supported(P, Bt.n_max, block, &why)) return fail(SLOS_EUNSUPPORTED, "fused backward: " + why);
     const int64_t Np = Bt.n_max >= 2 ? P.N[Bt.n_max - 1] : 1;
-    void* fn = pick_bwd(block, P.m, Np, restricted_plan(P));
+    void* fn = kind == 2 ? pick_bwd_clicks(block, P.m, Np) : pick_bwd(block, P.m, Np, restricted_plan(P));
     if (!fn) return fail(SLOS_EUNSUPPORTED, "fused backward: no kernel instance for this shape");
     const size_t base = bwd_lds_for_block(P, Bt.n_max, block);
     (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P.max_lds);
@@ -1265,7 +1291,7 @@ int launch_fused_bwd(const slos_batch_s& Bt, int block, const float2* U, const v
     }
     const int grid = grid_for(P, fn, block, lds, Bt.B);
     const int S = (int)(lds_bwd_states(P, Bt.n_max) + kept);
-    int pr = probs ? 1 : 0;
+    int pr = kind != 0 ? 1 : 0;
     void* args[] = {(void*)&P.m, (void*)&P.d_layers, (void*)&Bt.dev, (void*)&U, (void*)&gin, (void*)&gU,
                     (void*)&S, (void*)&pr, (void*)&KR};
     hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, stream);

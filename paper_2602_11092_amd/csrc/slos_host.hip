@@ -932,14 +932,15 @@ int run_expect(const slos_batch_s& Bt, int op, int v, int blk, const float* U, c
     }
     rc = launch_expand_mode_weights(Bt, (const float*)gin, pv, clicks, s);
     if (rc != SLOS_OK) return rc;
-    return fused ? launch_fused_bwd(Bt, blk, (const float2*)U, pv, true, (float2*)out, s)
+    return fused ? launch_fused_bwd(Bt, blk, (const float2*)U, pv, 1, (float2*)out, s)
                  : launch_layered_bwd(Bt, blk, (const float2*)U, pv, true, (float2*)out, rest, s);
 }
 
 // Threshold-detector click probabilities and their adjoint: p (or dL/dp)
 // lives at the start of the workspace; the forward gathers each pattern's
 // states (inside the fused forward where its LDS holds a run of patterns),
-// the adjoint scatters dL/dP back onto them.
+// the fused adjoint of the full space reads dL/dP through the states' patterns,
+// the others have it scattered onto the states first.
 int run_threshold(const slos_batch_s& Bt, int op, int v, int blk, const float* U, const void* gin, void* out,
                   void* ws, size_t ws_bytes, hipStream_t s, const std::string& nm) {
     if (!(Bt.plan->flags & SLOS_PLAN_THRESHOLD))
@@ -963,9 +964,11 @@ int run_threshold(const slos_batch_s& Bt, int op, int v, int blk, const float* U
         if (rc == SLOS_OK) rc = launch_threshold_gather(Bt, pv, (float*)out, s);
         return rc;
     }
+    if (fused && (Bt.plan->flags & (SLOS_PLAN_UNBUNCHED | SLOS_PLAN_DUAL_RAIL)) == 0)
+        return launch_fused_bwd(Bt, blk, (const float2*)U, gin, 2, (float2*)out, s);
     rc = launch_threshold_scatter(Bt, (const float*)gin, pv, s);
     if (rc != SLOS_OK) return rc;
-    return fused ? launch_fused_bwd(Bt, blk, (const float2*)U, pv, true, (float2*)out, s)
+    return fused ? launch_fused_bwd(Bt, blk, (const float2*)U, pv, 1, (float2*)out, s)
                  : launch_layered_bwd(Bt, blk, (const float2*)U, pv, true, (float2*)out, rest, s);
 }
 
@@ -995,7 +998,7 @@ int run(slos_batch_t batch, int op, const float* U, const void* gin, void* out, 
     if (v == SLOS_VARIANT_FUSED_PAIRS && !bwd) {
         rc = launch_fused_pairs_fwd(*batch, blk, pairs_tile(*batch, op), (const float2*)U, out, probs, s);
     } else if (v == SLOS_VARIANT_FUSED) {
-        rc = bwd ? launch_fused_bwd(*batch, blk, (const float2*)U, gin, probs, (float2*)out, s)
+        rc = bwd ? launch_fused_bwd(*batch, blk, (const float2*)U, gin, probs ? 1 : 0, (float2*)out, s)
                  : launch_fused_fwd(*batch, blk, (const float2*)U, out, probs ? 1 : 0, s);
     } else {
         const bool halves = auto_halves(*batch, op);

@@ -151,6 +151,7 @@ size_t fused_bwd_lds_bytes(const slos_plan_s& P, int n_max);
 bool fused_fwd_supported(const slos_plan_s& P, int n_max, int block, std::string* why, bool expect = false);
 // the fused adjoint's instances for restricted-space plans (slos_fused_r.hip)
 void* pick_bwd_restricted(int block, int m, int64_t Np);
+void* pick_bwd_clicks(int block, int m, int64_t Np);
 // successors that leave a restricted space are marked so in the successor tables
 constexpr uint32_t kNoSuccessor = 0xFFFFFFF8u;  // (uint32)(-1) << 3
 inline bool restricted_plan(const slos_plan_s& P) { return (P.flags & (SLOS_PLAN_UNBUNCHED | SLOS_PLAN_DUAL_RAIL)) != 0; }
@@ -162,7 +163,8 @@ int fused_default_block(const slos_plan_s& P, int n_max, bool backward);
 // click probabilities (both [B][m] floats)
 int launch_fused_fwd(const slos_batch_s& Bt, int block, const float2* U, void* out, int epi,
                      hipStream_t stream);
-int launch_fused_bwd(const slos_batch_s& Bt, int block, const float2* U, const void* gin, bool probs,
+// kind: 0 dL/da, 1 dL/dp, 2 dL/dP of the click patterns (full space)
+int launch_fused_bwd(const slos_batch_s& Bt, int block, const float2* U, const void* gin, int kind,
                      float2* gU, hipStream_t stream);
 
 // ---- two samples per workgroup (forward amplitudes and probabilities): slos_fused2.hip ----
