@@ -37,7 +37,7 @@ constexpr int kUcolSlots = 33;
 
 // One photon layer k of the transition graph (all k-photon states over m
 // modes, in basis order).  Device pointers.
-struct LayerDev {
+struct alignas(64) LayerDev {  // what every kernel reads lies in the first line
     const uint4* predv;     // [ngrp][N] groups of four predecessor entries: entries 4g..4g+3
                             // of t's sorted mode list (empty past k or where a mode repeats)
     const uint32_t* succ;   // [ceil(m/4)][N_{k-1}][4]: entry j & 3 of group j / 4 is the byte
