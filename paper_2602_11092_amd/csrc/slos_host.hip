@@ -1123,6 +1123,7 @@ extern "C" int slos_superposition_create(slos_batch_t components, int G, const i
     std::vector<uint32_t> gcols(std::max(G, 1), 0u);
     bool dense = G > 0;
     std::vector<Counter> ranks;
+    std::vector<char> seen;
     for (int n = 0; n <= Bt.n_max && dense; ++n) ranks.emplace_back(Bt.plan->m, n);
     for (int g = 0; g < G && dense; ++g) {
         const int64_t c0 = group_off[g], c1 = group_off[g + 1];
@@ -1131,7 +1132,7 @@ extern "C" int slos_superposition_create(slos_batch_t components, int G, const i
         if (!dense) break;
         S->dev.n_present |= 1u << n;
         const Counter& C = ranks[n];
-        std::vector<char> seen((size_t)Bt.plan->N[n], 0);
+        seen.assign((size_t)Bt.plan->N[n], 0);
         for (int64_t c = c0; c < c1; ++c) {
             const int32_t* L = &Bt.modes_host[(size_t)c * kMaxPhotons];
             crank[c] = (int32_t)C.rank(L, n);
@@ -1156,12 +1157,15 @@ extern "C" int slos_superposition_create(slos_batch_t components, int G, const i
         return fail(SLOS_ENOMEM, "slos_superposition_create: hipMalloc failed");
     }
     char* base = (char*)S->dmem;
-    hipError_t e = hipMemcpy(base + o_grp, group.data(), group.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(base + o_goff, S->goff.data(), (G + 1) * 8, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(base + o_ooff, S->ooff.data(), (G + 1) * 8, hipMemcpyHostToDevice);
-    if (e == hipSuccess && dense) e = hipMemcpy(base + o_cr, crank.data(), crank.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess && dense) e = hipMemcpy(base + o_cn, cnorm.data(), cnorm.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess && dense) e = hipMemcpy(base + o_gc, gcols.data(), gcols.size() * 4, hipMemcpyHostToDevice);
+    std::vector<char> host(total);  // one upload
+    auto put = [&](size_t o, const void* src, size_t bytes) { std::memcpy(host.data() + o, src, bytes); };
+    put(o_grp, group.data(), group.size() * 4);
+    put(o_goff, S->goff.data(), (G + 1) * 8);
+    put(o_ooff, S->ooff.data(), (G + 1) * 8);
+    put(o_cr, crank.data(), crank.size() * 4);
+    put(o_cn, cnorm.data(), cnorm.size() * 4);
+    put(o_gc, gcols.data(), gcols.size() * 4);
+    hipError_t e = hipMemcpy(base, host.data(), total, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         hipFree(S->dmem);
         delete S;
