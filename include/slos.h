@@ -407,8 +407,9 @@ SLOS_API int fock_threshold_probs(slos_batch_t batch, const float* U, float* out
                                   void* ws, size_t ws_bytes, void* stream);
 
 /* grad_U <- dL/dU given grad_out = dL/dP (device, float, [threshold_len]):
- * dL/dp_t = dL/dP(pattern of t) in the workspace, then the probability
- * adjoint.  Plans with successor tables only. */
+ * the probability adjoint with dL/dp_t = dL/dP(pattern of t), read through the
+ * states' patterns by the fused variant of the full space and formed in the
+ * workspace otherwise.  Plans with successor tables only. */
 SLOS_API int fock_threshold_probs_backward(slos_batch_t batch, const float* U, const float* grad_out,
                                            float* grad_U, void* ws, size_t ws_bytes, void* stream);
 

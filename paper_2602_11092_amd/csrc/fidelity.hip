@@ -6,12 +6,9 @@
 //
 // where C lists the input modes with multiplicity (n x n; Cauchy-Binet over
 // the output basis turns the inner product of two C(m+n-1, n)-dimensional
-// vectors into one n x n permanent).  Perm(M) by Ryser's formula,
-//   Perm(M) = (-1)^n sum_{S subset of [n]} (-1)^|S| prod_i sum_{j in S} M[i][j],
-// with the subsets walked in Gray-code order so that each step changes one
-// column of the row sums.  FP64 arithmetic on the complex64 inputs (the
-// chip's FP64 vector rate equals its unpacked FP32 rate, and Ryser's sum
-// cancels strongly).
+// vectors into one n x n permanent).  FP64 arithmetic on the complex64 inputs
+// (the chip's FP64 vector rate equals its unpacked FP32 rate, and the
+// permanent's sums of signed products cancel strongly).
 //
 // Two kernels:
 //  * n <= 8: a workgroup takes a 16 x 16 tile of (a, b) pairs and stages the
@@ -34,8 +31,10 @@
 //    reads); n = 8 on two: 116 -> 190.
 //  * n >= 9 (and n = 0): one wave per pair.  Its lanes build M in LDS, then
 //    lane l walks the Gray-code positions [l K, (l+1) K), K = ceil(2^n / 64),
-//    of Ryser's formula from row sums formed directly; a fixed-order shuffle
-//    reduction combines the lanes.
+//    of Ryser's formula,
+//      Perm(M) = (-1)^n sum_{S subset of [n]} (-1)^|S| prod_i sum_{j in S} M[i][j],
+//    from row sums formed directly, one column added or removed per step; a
+//    fixed-order shuffle reduction combines the lanes.
 #include "slos_internal.h"
 
 namespace slos {

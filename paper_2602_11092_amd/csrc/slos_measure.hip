@@ -9,9 +9,11 @@
 //    probabilities of threshold detectors and their adjoint)
 //   P_b(c)       = sum of p_b over the states of click pattern c
 //                                         (threshold_gather_kernel)
-//   dL/dp_b[t]   = dL/dP_b(pattern of t)  (threshold_scatter_kernel)
-//   cdf_b[t]     = sum_{t' <= t} p_b[t'], FP64 (cdf_partial_kernel, cdf_scan_kernel)
-//   shot         = first t with cdf_b[t] > u cdf_b[N-1]  (sample_kernel)
+//   dL/dp_b[t]   = dL/dP_b(pattern of t)  (threshold_scatter_kernel; the fused
+//                                         adjoint of the full space reads dL/dP itself)
+//   cdf_b[t]     = sum_{t' <= t} p_b[t'], FP64
+//   shot         = first t with cdf_b[t] > u cdf_b[N-1]  (sample_direct_kernel, run
+//                   sums in LDS; large samples cdf_partial_kernel, cdf_scan_kernel, sample_kernel)
 //
 // A state's photons are read from its predecessor entries in the transition
 // table of its photon layer (for_each_photon).  Workgroup b * C + c takes
