@@ -665,10 +665,11 @@ def bench_extension(args, dev):
         ws = batch.workspace(B.OP_MODE_EXPECTATIONS, dev)
         step = lambda: B.fock_mode_expectations(batch, U, out=out, ws=ws)
         work, unit = Bn * math.comb(m + n - 1, n), "Fock states/s"
-        flop = Bn * slos_fwd_flop(m, n)
+        # the Gram matrix, its minors' permanents over column subsets, and the contraction
+        flop = Bn * 8.0 * (2 * n * n * m + 3 * n * 2 ** (n - 1))
         oracle_one = lambda b: O.mode_expectations(Uh[b], occ[b])
         check = lambda b, r: float(np.abs(out[b].cpu().numpy() - r).max())
-        cfg = "fused last-layer epilogue, p never written"
+        cfg = "closed form: permanents of the Gram matrix's minors, FP64, no Fock space"
     elif name.startswith("threshold"):
         batch = B.Batch(B.Plan(m, n, threshold=True), occ)
         out = torch.empty(batch.threshold_len, dtype=torch.float32, device=dev)
@@ -764,19 +765,24 @@ def bench_extension(args, dev):
         ws = sup.workspace(False, dev)
         step = lambda: B.fock_superposition_amplitudes(sup, Ug, x, out=out, ws=ws)
         work, unit = Bn * N, "output amplitudes/s"
-        flop = Bn * N * (slos_fwd_flop(m, n) + 8.0 * N)  # one SLOS per component + the weighted combine
+        # step k: one photon of every state, N_k N_{n-k} m complex MACs
+        flop = Bn * 8.0 * m * sum(math.comb(m + k - 1, k) * math.comb(m + n - k - 1, n - k) for k in range(1, n + 1))
         xh = x.cpu().numpy().astype(np.complex128)
         oracle_one = lambda b: O.superposition_amplitudes(Uh[b], occ[b * N:(b + 1) * N], xh[b * N:(b + 1) * N])
         check = lambda b, r: float(np.abs(out[b * N:(b + 1) * N].cpu().numpy() - r).max())
-        cfg = "dense inputs: every basis state a component; one SLOS per component + combine"
+        cfg = "dense inputs: every basis state a component; the whole superposition photon by photon"
     else:
         out = torch.empty((Bn, Bn), dtype=torch.float32, device=dev)
         step = lambda: B.fock_fidelity_kernel(occ, U, out=out)
         work, unit = Bn * Bn, "kernel entries/s"
-        flop = Bn * Bn * (8.0 * n * n * m + (2 ** n) * (2 * n + 6 * (n - 1)))
+        # M and Glynn's 2^(n-1) terms, on and above the diagonal in tiles of 16 x 16 pairs
+        # (n >= 9: Ryser's 2^n terms for every pair)
+        tiles = (Bn + 15) // 16
+        pairs = 256 * tiles * (tiles + 1) // 2 if n <= 8 else Bn * Bn
+        flop = pairs * (8.0 * n * n * m + 2 ** (n - 1 if n <= 8 else n) * (2 * n + 6 * (n - 1)))
         oracle_one = lambda b: np.array([O.fidelity(Uh[b], Uh[c], occ) for c in range(32)])
         check = lambda b, r: float(np.abs(out[b, :32].cpu().numpy() - r).max())
-        cfg = "thread per pair, FP64 Ryser with unrolled Gray code (oracle: 32 entries per sampled row)"
+        cfg = "FP64 permanents of tiles of pairs, the Gram matrix mirrored (oracle: 32 entries per sampled row)"
         oracle_units = 32
 
     for _ in range(args.warmup):

@@ -4,7 +4,7 @@
 //
 // Layer by layer, every state of such a space is gathered from up to n states
 // far apart in a layer larger than the caches (m = 24, n = 8, 16 samples: the last
-// layer fetches 4 GB, a line at a time, for 0.5 GB of probabilities; 0.99 ms the
+// layer fetches 3.1 GB, a line at a time, for 0.5 GB of probabilities; 0.99 ms the
 // forward).
 // The halves' factors are 8.3 MB per half and sample, read in tiles; the cost is
 // arithmetic instead, 47 complex products per output at the FP32 matrix rate.
