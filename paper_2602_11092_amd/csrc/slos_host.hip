@@ -639,6 +639,8 @@ extern "C" int slos_batch_create(slos_plan_t plan, int B, const int32_t* occ_hos
     std::vector<int32_t>& modes = Bt->modes_host;
     modes.assign((size_t)std::max(B, 1) * kMaxPhotons, 0);
     std::vector<float> innorm(std::max(B, 1), 1.f);
+    std::vector<int64_t> thr(plan->n_max + 1);
+    for (int n = 0; n <= plan->n_max; ++n) thr[n] = threshold_dim(m, n);
     for (int b = 0; b < B; ++b) {
         int n = 0;
         double f = 1.0;
@@ -658,7 +660,7 @@ extern "C" int slos_batch_create(slos_plan_t plan, int B, const int32_t* occ_hos
         Bt->n_host[b] = n;
         innorm[b] = (float)(1.0 / std::sqrt(f));
         Bt->off_host[b + 1] = Bt->off_host[b] + plan->N[n];
-        Bt->thr_off_host[b + 1] = Bt->thr_off_host[b] + threshold_dim(m, n);
+        Bt->thr_off_host[b + 1] = Bt->thr_off_host[b] + thr[n];
         Bt->n_max = std::max(Bt->n_max, n);
         Bt->n_min = b == 0 ? n : std::min(Bt->n_min, n);
     }
