@@ -36,8 +36,14 @@ namespace {
 // four per CU (its registers allow 4 waves per SIMD): m = 24, n = 8, 16 samples
 // 2175 us with 1024, 2327 with 768 and 2339 with 2048.  A layer launch keeps about 5
 // per CU: m = 20, n = 6, 512 samples 1321 us with 2560 over all groups, 1643 with 2048
-// for each group.
+// for each group; a layer that 2560 blocks cover is given all it needs (m = 28,
+// n = 5, 2 samples 21 us in 1280).
 constexpr int kPullBlocks = 1024, kLayerBlocks = 2560;
+// Values (states x samples) of a layer from which its lanes take two samples:
+// smaller ones do not fill the chip and run on more wavefronts (forward, us: m = 12,
+// n = 8, 3 samples 34 with pairs throughout, 28.5 now; m = 16, n = 7, 1 sample 25 and
+// 23; m = 20, n = 6, 3 samples 24.9, 23.9 and 25.4 from 2^16, 2^19 and 2^20 values).
+constexpr int64_t kPairLanes = 1 << 19;
 // The lanes of a state share its successors, a part of the modes each: 2 parts for
 // lanes of two samples (4: m = 24, n = 8, 16 samples 2398 us against 2175), 4 for a
 // lone sample (1, 2, 4, 8 parts: 624, 370, 333, 361 us).
@@ -62,7 +68,7 @@ Shape shape_of(const slos_batch_s& Bt) {
     const int64_t need = (Nmax * sg + 255) / 256 * (sg > 1 ? 1 : kParts1);
     const int cap = std::max(8, std::min(kPullBlocks, 2 * kPullBlocks / ngrp));
     int gx = (int)std::max<int64_t>(1, std::min<int64_t>(need, cap));
-    if (gx >= 64) gx &= ~7;
+    if (gx >= 64) gx = (gx + 7) & ~7;
     return Shape{sg, ngrp, gx};
 }
 
@@ -70,7 +76,7 @@ Shape shape_of(const slos_batch_s& Bt) {
 __host__ __device__ __forceinline__ int pull_blocks(int64_t Nprev, int SG, int GX) {
     const int64_t need = (Nprev * (SG > 1 ? SG / 2 * kParts2 : kParts1) + 255) / 256;
     const int gx = need < GX ? (int)need : GX;
-    return gx >= 64 ? gx & ~7 : gx;
+    return gx >= 64 ? (gx + 7) & ~7 : gx;  // (GX, too, is a multiple of 8 from 64 on)
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -173,19 +179,29 @@ __global__ __launch_bounds__(BLOCK) void layered_layer_kernel(int m, const Layer
     const int tl = tid / per;
     const int TPB = BLOCK / per;
     const int g = blockIdx.y;
-    bool active[V], top[V], any = false, all = true;
+    // what the first state needs besides the column is on its way while the
+    // column is staged
+    const int N = (int)ldc(&Ls[k].N), Nprev = (int)ldc(&Ls[k - 1].N);
+    const int sh = ldc(&Ls[k].pred_shift), ngrp = ldc(&Ls[k].ngrp);
+    const uint4* predv = ldc(&Ls[k].predv);
+    const float* nrms = ldc(&Ls[k].nrm);
+    const uint32_t rmask = pred_rank_mask(sh);
+    const bool need_d = !(mode == kSeed && !PROBS), table = need_d && k > 1;
+    const Range R = block_range(N, TPB, tl);
+    uint4 e0 = {}, e1 = {};
+    if (table && R.t < R.end) {
+        e0 = predv[R.t];
+        if (ngrp > 1) e1 = predv[(size_t)N + R.t];
+    }
+    int n_b[V];
     float innorm[V];
     int64_t off[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        const int b = g * SG + bl + v;
-        const int n_b = b < Bt.B ? Bt.n[b] : -1;
-        active[v] = mode == kForward ? n_b >= k : mode == kRecompute ? n_b > k : n_b == k;
-        top[v] = n_b == k;
-        any |= active[v];
-        all &= active[v];
-        innorm[v] = active[v] ? Bt.innorm[b] : 0.f;
-        off[v] = active[v] ? Bt.off[b] : 0;
+        const int b = min(g * SG + bl + v, Bt.B - 1);
+        n_b[v] = Bt.n[b];
+        innorm[v] = Bt.innorm[b];
+        off[v] = Bt.off[b];
     }
     // stage column i_k of U for every sample of the group (slot 32 = 0)
     for (int q = tid; q < SG; q += BLOCK) us[32 * SG + q] = c_zero();
@@ -198,23 +214,20 @@ __global__ __launch_bounds__(BLOCK) void layered_layer_kernel(int m, const Layer
         }
     }
     __syncthreads();
-    if (!any) return;
-    const LayerDev L = Ls[k];
-    const int N = (int)L.N;
-    const int Nprev = (int)Ls[k - 1].N;
-    const int sh = L.pred_shift, ngrp = L.ngrp;
-    const uint32_t rmask = pred_rank_mask(sh);
-    const bool need_d = !(mode == kSeed && !PROBS), table = need_d && k > 1;
-    const float2* pg = prev + (size_t)g * Nprev * SG + bl;
-    const Range R = block_range(N, TPB, tl);
-    uint4 e0 = {}, e1 = {};
-    if (table && R.t < R.end) {
-        e0 = L.predv[R.t];
-        if (ngrp > 1) e1 = L.predv[(size_t)N + R.t];
+    bool active[V], top[V], any = false, all = true;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const bool here = g * SG + bl + v < Bt.B;
+        active[v] = here && (mode == kForward ? n_b[v] >= k : mode == kRecompute ? n_b[v] > k : n_b[v] == k);
+        top[v] = n_b[v] == k;
+        any |= active[v];
+        all &= active[v];
     }
+    if (!any) return;
+    const float2* pg = prev + (size_t)g * Nprev * SG + bl;
     for (int t = R.t; t < R.end; t += R.step) {
         // (the state's norm and incoming gradient fly with its gathers)
-        const float nrm = mode == kRecompute ? 0.f : L.nrm[t];
+        const float nrm = mode == kRecompute ? 0.f : nrms[t];
         Vec<V> acc;
         float2 gi[V];
 #pragma unroll
@@ -235,9 +248,10 @@ __global__ __launch_bounds__(BLOCK) void layered_layer_kernel(int m, const Layer
 #pragma unroll
                 for (int q = 4; q < 8; ++q) d[q] = ld_vec<V>(pg + (size_t)((es[q] & rmask) >> 3) * SG);
             }
-            const int tn = t + R.step < R.end ? t + R.step : t;
-            e0 = L.predv[tn];
-            if (ngrp > 1) e1 = L.predv[(size_t)N + tn];
+            if (t + R.step < R.end) {
+                e0 = predv[t + R.step];
+                if (ngrp > 1) e1 = predv[(size_t)N + t + R.step];
+            }
             // empty entries name the zero slot 32 of the coefficient column
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -254,7 +268,7 @@ __global__ __launch_bounds__(BLOCK) void layered_layer_kernel(int m, const Layer
                 }
             }
             for (int gq = 2; gq < ngrp; ++gq) {
-                const uint4 e4 = L.predv[(size_t)gq * N + t];
+                const uint4 e4 = predv[(size_t)gq * N + t];
                 const uint32_t ex[4] = {e4.x, e4.y, e4.z, e4.w};
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -495,14 +509,15 @@ int launch_layer(const slos_batch_s& Bt, int block, const float2* U, int k, int 
     const slos_plan_s& P = *Bt.plan;
     const Shape sh = shape_of(Bt);
     if (block < sh.SG) block = sh.SG;
-    const int V = sh.SG > 1 ? 2 : 1;
+    const int V = sh.SG > 1 && P.N[k] * sh.SG * sh.NGRP >= kPairLanes ? 2 : 1;
     void* fn = V == 2 ? (probs ? layer_fn<true, 2>(block) : layer_fn<false, 2>(block))
                       : (probs ? layer_fn<true, 1>(block) : layer_fn<false, 1>(block));
     if (!fn) return fail(SLOS_EUNSUPPORTED, "layered: bad block size");
     const int TPB = block / (sh.SG / V);
     const int64_t N = P.N[k];
-    int gx = (int)std::max<int64_t>(1, std::min<int64_t>((N + TPB - 1) / TPB, std::max(8, std::min(1280, kLayerBlocks / sh.NGRP))));
-    if (gx >= 64) gx &= ~7;
+    const int64_t need = (N + TPB - 1) / TPB;
+    int gx = (int)(need * sh.NGRP <= kLayerBlocks ? need : std::max(8, std::min(kLayerBlocks / 2, kLayerBlocks / sh.NGRP)));
+    if (gx >= 64) gx = (gx + 7) & ~7;
     int m = P.m;
     const LayerDev* Ls = P.d_layers;
     int SG = sh.SG;
