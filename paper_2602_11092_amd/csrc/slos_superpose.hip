@@ -20,8 +20,11 @@
 //   gT_k[J][I] = sum_{j <= first(J)} sum_{i in I} conj(U[j][i]) gT_{k+1}[J + e_j][I - e_i],
 //   gU[j][i]  += sum conj(T_k[J][I' + e_i]) gT_{k+1}[J + e_j][I']  over J with first(J) >= j and I'.
 //
+// T and the sums it takes are FP32; gT is carried in FP64, so that dL/dx (gT_0,
+// scaled) is rounded once.
+//
 // One workgroup per input; T, gT, U and 16-bit copies of the transition
-// tables sit in LDS (m = 6, n = 3: 7 KB).  The kernels are bound by the
+// tables sit in LDS (m = 6, n = 3: 9 KB).  The kernels are bound by the
 // latency of their 2 n short steps, and overlap over the inputs of a CU.
 // Fixed summation orders throughout: results are bitwise reproducible.
 // Measured at m = 6, n = 3, 1024 inputs of 56 components, against one
@@ -36,7 +39,7 @@ constexpr int kDenseBlock = 128;
 // LDS plan of an n-photon input (bytes).
 struct DenseLayout {
     uint32_t T[kMaxPhotons + 1];     // T_k, float2 [N_k][N_{n-k}]
-    uint32_t g[2];                   // gT of the step and of the one above (backward)
+    uint32_t g[2];                   // gT of the step and of the one above, double2 (backward)
     uint32_t U;                      // float2 [m][m]
     uint32_t part;                   // float2 [kDenseBlock]: partial sums of gU (backward)
     uint32_t succ[kMaxPhotons + 1];  // uint16 [N_{l-1}][m], l = 1..n: rank of I' + e_i
@@ -52,9 +55,10 @@ __host__ __device__ inline void dense_layout(const int* N, int m, int n, bool bw
         if (k < n || !bwd) at += b;  // the adjoint starts from the given gradient, not from T_n
         most = b > most ? b : most;
     }
+    if (bwd) at = (at + 15u) & ~15u;
     L.g[0] = at;
-    L.g[1] = at + (bwd ? most : 0);
-    at += bwd ? 2 * most : 0;
+    L.g[1] = at + (bwd ? 2 * most : 0);
+    at += bwd ? 4 * most : 0;
     L.U = at;
     at += 8u * (uint32_t)(m * m);
     L.part = at;
@@ -86,6 +90,18 @@ struct DenseArgs {
     float2* gU;              // [G][m][m] (backward)
     float2* gx;              // [C] or nullptr (backward)
 };
+
+// prod t! of the state whose n removals are pred (a mode's further photons are
+// marked 0xFFFF).
+__device__ __forceinline__ double fact_of(const uint16_t* pred, int n) {
+    double f = 1.0;
+    int run = 1;
+    for (int q = 0; q < n; ++q) {
+        run = pred[2 * q] == 0xFFFF ? run + 1 : 1;
+        f *= run;
+    }
+    return f;
+}
 
 // T_0 .. T_{n-1} (backward) or T_n (forward) of input g in LDS, with its tables.
 template <bool BWD>
@@ -150,9 +166,13 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
         for (int t = tid; t < N[n]; t += kDenseBlock)
             A.y[o0 + t] = n > 0 ? c_scale(Tn[t], 1.f / ldg(nrm + t)) : Tn[t];
     } else {
-        float2* gn = (float2*)(dlds + L.g[n & 1]);  // gT_k at g[k & 1]
-        for (int t = tid; t < N[n]; t += kDenseBlock)
-            gn[t] = n > 0 ? c_scale(A.gy[o0 + t], 1.f / ldg(nrm + t)) : A.gy[o0 + t];
+        double2* gn = (double2*)(dlds + L.g[n & 1]);  // gT_k at g[k & 1]
+        const uint16_t* predn = (const uint16_t*)(dlds + L.pred[n]);
+        for (int t = tid; t < N[n]; t += kDenseBlock) {
+            const float2 v = A.gy[o0 + t];
+            const double s = 1.0 / sqrt(fact_of(predn + 2 * t * n, n));
+            gn[t] = make_double2(s * v.x, s * v.y);
+        }
         __syncthreads();
         // thread (i, j, part): this part's share of gU[j][i]
         const int mm = m * m;
@@ -162,8 +182,8 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
         for (auto& v : gu) v = c_zero();
         for (int k = n - 1; k >= 0; --k) {
             const float2* Tk = (const float2*)(dlds + L.T[k]);
-            const float2* gu1 = (const float2*)(dlds + L.g[(k + 1) & 1]);
-            float2* gk = (float2*)(dlds + L.g[k & 1]);
+            const double2* gu1 = (const double2*)(dlds + L.g[(k + 1) & 1]);
+            double2* gk = (double2*)(dlds + L.g[k & 1]);
             const uint16_t* succI = (const uint16_t*)(dlds + L.succ[n - k]);
             const uint16_t* succJ = (const uint16_t*)(dlds + L.succ[k + 1]);
             const uint16_t* predJ = (const uint16_t*)(dlds + L.pred[k + 1]);
@@ -179,27 +199,40 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
                 const int lo = ldg(minoff + j), hi = ldg(minoff + j + 1);
                 for (int r = lo; r < hi; ++r) {
                     const float2* t = Tk + predJ[2 * r * (k + 1) + 1] * cols_k;
-                    for (int q = part; q < cols_n; q += parts) c_fma_conj(gu[w], t[succI[q * m + i]], gu1[r * cols_n + q]);
+                    for (int q = part; q < cols_n; q += parts) {
+                        const double2 v = gu1[r * cols_n + q];
+                        c_fma_conj(gu[w], t[succI[q * m + i]], make_float2((float)v.x, (float)v.y));
+                    }
                 }
             }
             for (int e = tid; e < N[k] * cols_k; e += kDenseBlock) {
                 const int J = e / cols_k, I = e % cols_k;
                 const int first = k > 0 ? firstJ[2 * J * k] : m - 1;
-                float2 acc = c_zero();
+                double2 acc = make_double2(0.0, 0.0);
                 for (int p = 0; p < n - k; ++p) {
                     const int i = predI[2 * (I * (n - k) + p)];
                     if (i == 0xFFFF) continue;
-                    const float2* gq = gu1 + predI[2 * (I * (n - k) + p) + 1];
-                    for (int j = 0; j <= first; ++j) c_fma_conj(acc, U[j * m + i], gq[succJ[J * m + j] * cols_n]);
+                    const double2* gq = gu1 + predI[2 * (I * (n - k) + p) + 1];
+                    for (int j = 0; j <= first; ++j) {  // acc += conj(U[j][i]) g
+                        const float2 u = U[j * m + i];
+                        const double2 v = gq[succJ[J * m + j] * cols_n];
+                        acc.x = fma((double)u.x, v.x, acc.x);
+                        acc.x = fma((double)u.y, v.y, acc.x);
+                        acc.y = fma((double)u.x, v.y, acc.y);
+                        acc.y = fma(-(double)u.y, v.x, acc.y);
+                    }
                 }
                 gk[e] = acc;
             }
             __syncthreads();
         }
         if (A.gx) {
-            const float2* g0 = (const float2*)(dlds + L.g[0]);
-            for (int64_t c = c0 + tid; c < c1; c += kDenseBlock)
-                A.gx[c] = c_scale(g0[ldg(A.crank + c)], ldg(A.cnorm + c));
+            const double2* g0 = (const double2*)(dlds + L.g[0]);
+            for (int64_t c = c0 + tid; c < c1; c += kDenseBlock) {
+                const int s = ldg(A.crank + c);
+                const double f = sqrt(fact_of(predn + 2 * s * n, n));
+                A.gx[c] = make_float2((float)(f * g0[s].x), (float)(f * g0[s].y));
+            }
         }
         float2* part = (float2*)(dlds + L.part);
         if (parts > 1) {  // one pass: parts * mm <= kDenseBlock
@@ -232,8 +265,8 @@ size_t dense_lds(const slos_plan_s& P, int n, bool bwd) {
 
 // The rule, per group: one input of `comps` distinct components of n photons
 // goes through the steps above where they take no more products than one
-// simulation per component, and its adjoint fits in 64 KB of LDS (two
-// workgroups a CU).  At the line the steps already win, their cost being
+// simulation per component, and its adjoint fits in 88 KB of LDS (most take
+// half of that or less: two workgroups a CU or more).  At the line the steps already win, their cost being
 // latency (us, forward / adjoint, steps against components): m = 6, n = 3, 9 of
 // 56 states, 1024 inputs 9.9 / 21 against 38 / 177; m = 4, n = 2, 5 of 10 states,
 // 256 inputs 14.5 / 14.7 (a call's cost on the host) against 18.7 / 33; m = 8,
@@ -248,7 +281,7 @@ bool dense_superposition_ok(const slos_plan_s& P, int n, int64_t comps) {
         steps += P.N[k] * P.N[n - k] * P.m;
         single += k * P.N[k];
     }
-    return steps <= single * comps && dense_lds(P, n, true) <= 65536;
+    return steps <= single * comps && dense_lds(P, n, true) <= 88 * 1024;
 }
 
 int launch_dense_superposition(const SupDev& S, const slos_batch_s& Bt, bool bwd, const float2* U, const float2* x,

@@ -97,3 +97,23 @@ def test_columns_no_component_uses_are_not_read():
     gU, gx = B.fock_superposition_amplitudes_backward(sup, to_dev_c64(U), x, torch.ones_like(out))
     assert torch.isfinite(torch.view_as_real(out)).all() and torch.isfinite(torch.view_as_real(gx)).all()
     assert torch.isfinite(torch.view_as_real(gU)).all() and torch.count_nonzero(gU[:, :, 2]) == 0
+
+
+@pytest.mark.parametrize("m,n", [(4, 2), (6, 3), (8, 3), (5, 4), (3, 6), (2, 9), (14, 3)])
+def test_grad_x_is_rounded_once(m, n):
+    # dL/dx_c = sum_t conj(a_c[t]) dL/dy_t, linear in float32 data: carried in 64
+    # bits, each part is off by its own rounding to float32, 2^-24 of it at most
+    rng = np.random.default_rng(10 * m + n)
+    occ = np.asarray(O.fock_basis(m, n), dtype=np.int32)
+    N = len(occ)
+    say("dL/dx of dense inputs", m, n)
+    U = W.haar_unitaries(rng, 1, m).astype(np.complex64)
+    x = (rng.standard_normal(N) + 1j * rng.standard_normal(N)).astype(np.complex64) / np.float32(np.sqrt(2 * N))
+    gy = (rng.standard_normal(N) + 1j * rng.standard_normal(N)).astype(np.complex64)
+    batch = B.Batch(B.Plan(m, n), occ)
+    sup = B.Superposition(batch, [0, N])
+    _, gx = B.fock_superposition_amplitudes_backward(sup, to_dev_c64(U), torch.from_numpy(x).to(DEV),
+                                                     torch.from_numpy(gy).to(DEV))
+    few = rng.permutation(N)[:64]
+    ref = np.array([np.vdot(O.amplitudes(widen(U[0]), occ[c]), gy.astype(np.complex128)) for c in few])
+    assert rel_err(gx.cpu().numpy()[few], ref) <= 2.0 ** -24 + 1e-12
