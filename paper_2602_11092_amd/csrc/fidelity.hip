@@ -107,10 +107,11 @@ __device__ __forceinline__ double2 glynn_sum(double2 (&rs)[N], const double2 (&M
 template <int N, int Q>
 __global__ __launch_bounds__(fid_tile(Q) * fid_tile(Q) << Q) void fidelity_tile_kernel(
     int m, FidModes C, double scale, const float2* __restrict__ U1, int B1, const float2* __restrict__ U2, int B2,
-    float* __restrict__ K, int tb, bool gram) {
+    float* __restrict__ K, int tb, unsigned tiles, bool gram) {
     constexpr int T = fid_tile(Q), LANES = 1 << Q, THREADS = T * T * LANES;
-    const int ty = (int)(blockIdx.x / (unsigned)tb), tx = (int)(blockIdx.x % (unsigned)tb);
-    if (gram && tx < ty) return;
+    const unsigned tile = blockIdx.y * gridDim.x + blockIdx.x;
+    const int ty = (int)(tile / (unsigned)tb), tx = (int)(tile % (unsigned)tb);
+    if (tile >= tiles || (gram && tx < ty)) return;
     // [2][m][N][T] columns of the tile's U1 and U2, widened once, then M of each pair (Q > 0)
     extern __shared__ double2 fid_lds[];
     const int tid = threadIdx.x;
@@ -363,12 +364,15 @@ extern "C" int fock_fidelity_kernel(int m, const int32_t* occ, const float* U1, 
                                           (void*)&fidelity_tile_kernel<7, 0>, (void*)&fidelity_tile_kernel<8, 2>};
         const size_t lds = (size_t)2 * T * m * n * sizeof(double2) + (q > 0 ? (size_t)n * n * T * T * sizeof(double2) : 0);
         int tb = (int)tb64;
+        unsigned tiles = (unsigned)(ta * tb64);
+        // a dimension of a launch holds less than 2^32 threads
+        const unsigned gx = std::min(tiles, 1u << 23), gy = (tiles + gx - 1) / gx;
         bool gram = U1 == U2 && B1 == B2;
         void* fn = tile_fns[n - 1];
         (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         void* args[] = {(void*)&m, (void*)&C, (void*)&scale, (void*)&U1, (void*)&B1, (void*)&U2, (void*)&B2, (void*)&K,
-                        (void*)&tb, (void*)&gram};
-        hipError_t e = hipLaunchKernel(fn, dim3((unsigned)(ta * tb64)), dim3(T * T << q), args, lds, (hipStream_t)stream);
+                        (void*)&tb, (void*)&tiles, (void*)&gram};
+        hipError_t e = hipLaunchKernel(fn, dim3(gx, gy), dim3(T * T << q), args, lds, (hipStream_t)stream);
         if (e != hipSuccess)
             return fail(SLOS_EHIP, std::string("fock_fidelity_kernel launch: ") + hipGetErrorString(e));
         return SLOS_OK;
