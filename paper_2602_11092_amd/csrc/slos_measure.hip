@@ -260,12 +260,14 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
 __global__ __launch_bounds__(kDirectBlock) void sample_direct_kernel(BatchDev Bt, const float* __restrict__ p,
                                                                      const float* __restrict__ u, int S, int parts,
-                                                                     int32_t* __restrict__ shots) {
+                                                                     unsigned groups, int32_t* __restrict__ shots) {
     constexpr int kWaves = kDirectBlock / 64;
     extern __shared__ double runs[];  // [R]: cumulative sums at the runs' ends
     __shared__ double wtot[kWaves];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int b = blockIdx.x / parts, part = blockIdx.x % parts;
+    const unsigned group = blockIdx.y * gridDim.x + blockIdx.x;
+    if (group >= groups) return;
+    const int b = (int)(group / (unsigned)parts), part = (int)(group % (unsigned)parts);
     const int64_t off = ldg(Bt.off + b);
     const int N = (int)(ldg(Bt.off + b + 1) - off);
     const float* pb = p + off;
@@ -496,9 +498,11 @@ int launch_sample(const slos_batch_s& Bt, const float* p, double* part, double* 
         int parts = (int)std::min<int64_t>(fill, ((int64_t)S + kDirectBlock - 1) / kDirectBlock);
         const size_t lds = (size_t)((Nmax + kRun - 1) / kRun) * sizeof(double);
         (void)hipFuncSetAttribute((void*)&sample_direct_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        void* args[] = {(void*)&Bt.dev, (void*)&p, (void*)&u, (void*)&S, (void*)&parts, (void*)&shots};
-        hipError_t e = hipLaunchKernel((void*)&sample_direct_kernel, dim3((unsigned)(Bt.B * parts)), dim3(kDirectBlock),
-                                       args, lds, stream);
+        // a dimension of a launch holds less than 2^32 threads
+        unsigned groups = (unsigned)Bt.B * (unsigned)parts;
+        const unsigned gx = std::min(groups, 1u << 21), gy = (groups + gx - 1) / gx;
+        void* args[] = {(void*)&Bt.dev, (void*)&p, (void*)&u, (void*)&S, (void*)&parts, (void*)&groups, (void*)&shots};
+        hipError_t e = hipLaunchKernel((void*)&sample_direct_kernel, dim3(gx, gy), dim3(kDirectBlock), args, lds, stream);
         if (e != hipSuccess) return fail(SLOS_EHIP, std::string("fock_sample launch: ") + hipGetErrorString(e));
         return SLOS_OK;
     }

@@ -30,3 +30,21 @@ def test_fidelity_of_more_tiles_than_a_launch_takes(n, B1, B2):
     u, v = U1.reshape(B1, 1).to(torch.complex128).abs(), U2.reshape(-1)[at].to(torch.complex128).abs()
     # FP64 arithmetic, rounded to FP32 once (values up to 1)
     assert (K[:, at].double() - (u * v) ** (2 * n)).abs().max().item() <= 2.0 ** -24 + 1e-12
+
+
+def test_shots_of_more_samples_than_a_launch_takes():
+    # one workgroup of 1024 threads per sample: 2^22 of them are too many
+    Bn = (1 << 22) + 2
+    say("samples past the launch limit", Bn)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    angle = torch.rand(Bn, device=DEV, generator=g) * 6.0
+    c, s = torch.cos(angle), torch.sin(angle)
+    U = torch.stack([c, -s, s, c], dim=1).reshape(Bn, 2, 2).to(torch.complex64)
+    batch = B.Batch(B.Plan(2, 1), np.tile(np.array([[1, 0]], dtype=np.int32), (Bn, 1)))
+    u = torch.rand((Bn, 1), device=DEV, generator=g)
+    shots = B.fock_sample(batch, U, u)
+    torch.cuda.synchronize()
+    # state 0 (the photon in mode 0) while u (p_0 + p_1) < p_0
+    p = B.fock_probs(batch, U).reshape(Bn, 2).double()
+    want = (u[:, 0].double() * p.sum(dim=1) >= p[:, 0]).to(torch.int32)
+    assert torch.equal(shots[:, 0], want)
