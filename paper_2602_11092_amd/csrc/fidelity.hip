@@ -10,10 +10,10 @@
 // (the chip's FP64 vector rate equals its unpacked FP32 rate, and the
 // permanent's sums of signed products cancel strongly).
 //
-// Two kernels:
-//  * n <= 8: a workgroup takes a 16 x 16 tile of (a, b) pairs and stages the
-//    input columns of its 32 unitaries in LDS (a thread's own loads of them
-//    are strided by a whole unitary: 64 cache lines an instruction, which is
+// Three kernels:
+//  * n <= 8: a workgroup takes a 16 x 16 tile of (a, b) pairs (8 x 8 at n = 8) and
+//    stages the input columns of its 32 (16) unitaries in LDS (a thread's own loads
+//    of them are strided by a whole unitary: 64 cache lines an instruction, which is
 //    what the time went into).  Perm(M) by Glynn's formula over column signs,
 //      Perm(M) = 2^(1-n) sum_{delta, delta_0 = 1} prod_j delta_j prod_i sum_j delta_j M[i][j],
 //    half of Ryser's terms, in Gray-code order and unrolled for the
@@ -29,7 +29,9 @@
 //    m = 20, n = 5, B = 512 82 / 28; m = 10, n = 7, B = 512 94 / 52; m = 12, n = 8,
 //    B = 512 846 / 116.  n = 6 and 7 on four lanes too: 30 -> 44 and 52 -> 55 (LDS
 //    reads); n = 8 on two: 116 -> 190.
-//  * n >= 9 (and n = 0): one wave per pair.  Its lanes build M in LDS, then
+//  * n = 3 to 7, K of a few long rows or columns: a thread per pair (the rule and
+//    both sides' times stand at fid_few_rows).
+//  * n >= 9 (and n = 0, and a single row at n = 8): one wave per pair.  Its lanes build M in LDS, then
 //    lane l walks the Gray-code positions [l K, (l+1) K), K = ceil(2^n / 64),
 //    of Ryser's formula,
 //      Perm(M) = (-1)^n sum_{S subset of [n]} (-1)^|S| prod_i sum_{j in S} M[i][j],
@@ -107,7 +109,7 @@ __device__ __forceinline__ double2 glynn_sum(double2 (&rs)[N], const double2 (&M
 template <int N, int Q>
 __global__ __launch_bounds__(fid_tile(Q) * fid_tile(Q) << Q) void fidelity_tile_kernel(
     int m, FidModes C, double scale, const float2* __restrict__ U1, int B1, const float2* __restrict__ U2, int B2,
-    float* __restrict__ K, int tb, unsigned tiles, bool gram) {
+    float* __restrict__ K, int tb, unsigned tiles, bool gram, bool cols) {
     constexpr int T = fid_tile(Q), LANES = 1 << Q, THREADS = T * T * LANES;
     const unsigned tile = blockIdx.y * gridDim.x + blockIdx.x;
     const int ty = (int)(tile / (unsigned)tb), tx = (int)(tile % (unsigned)tb);
@@ -129,8 +131,16 @@ __global__ __launch_bounds__(fid_tile(Q) * fid_tile(Q) << Q) void fidelity_tile_
         for (int c = 0; c < N; ++c) fid_lds[(row * N + c) * T + x] = make_double2(v[c].x, v[c].y);
     }
     __syncthreads();
+    // Up to n = 7 a wave's pairs are four rows a by 16 columns b (cols, for K of few
+    // columns: the other way round), so that where K ends inside a tile whole waves
+    // have no pairs and stop: one row of 131072 at m = 10, n = 4 31 us (67 when the
+    // rows past the last were computed too).
     const int pr = tid / LANES, part = tid % LANES;
-    const int xa = pr / T, xb = pr % T;
+    const int xa = Q == 0 && cols ? pr % T : pr / T, xb = Q == 0 && cols ? pr / T : pr % T;
+    if constexpr (Q == 0) {
+        const int first = __builtin_amdgcn_readfirstlane(pr / T);
+        if (cols ? b0 + first >= B2 : a0 + first >= B1) return;
+    }
     const double2* s1 = fid_lds + xa;
     const double2* s2 = fid_lds + T * m * N + xb;
     // columns NC part .. of M: M[r][c] = sum_k conj(U1[a][k][C_r]) U2[b][k][C_c]
@@ -241,6 +251,83 @@ __global__ __launch_bounds__(fid_tile(Q) * fid_tile(Q) << Q) void fidelity_tile_
     if (gram && a > b) return;  // the diagonal tile's lower half is mirrored too
     K[(int64_t)a * B2 + b] = v;
     if (gram && a < b) K[(int64_t)b * B2 + a] = v;
+}
+
+// A thread per pair, its columns read from memory (lanes of a wave share a):
+// Ryser's formula over the subsets in Gray-code order, from the empty set.
+template <int N>
+__global__ __launch_bounds__(kFidBlock) void fidelity_thread_kernel(int m, FidModes C, double scale,
+                                                                    const float2* __restrict__ U1, int B1,
+                                                                    const float2* __restrict__ U2, int B2,
+                                                                    float* __restrict__ K) {
+    const int64_t pair = (int64_t)blockIdx.x * kFidBlock + threadIdx.x;
+    if (pair >= (int64_t)B1 * B2) return;
+    const int64_t a = pair / B2, b = pair % B2;
+    const float2* u1 = U1 + a * m * m;
+    const float2* u2 = U2 + b * m * m;
+    // M[r][c] = sum_k conj(U1[a][k][C_r]) U2[b][k][C_c]
+    double2 M[N][N];
+#pragma unroll
+    for (int r = 0; r < N; ++r)
+#pragma unroll
+        for (int c = 0; c < N; ++c) M[r][c] = make_double2(0.0, 0.0);
+    for (int k = 0; k < m; ++k) {
+        double2 x[N], y[N];
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            const float2 v = u1[k * m + C.c[r]], w = u2[k * m + C.c[r]];
+            x[r] = make_double2(v.x, v.y);
+            y[r] = make_double2(w.x, w.y);
+        }
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+#pragma unroll
+            for (int c = 0; c < N; ++c) {
+                M[r][c].x += x[r].x * y[c].x + x[r].y * y[c].y;
+                M[r][c].y += x[r].x * y[c].y - x[r].y * y[c].x;
+            }
+    }
+    // Ryser over the subsets in Gray-code order, starting from the empty set
+    double2 rs[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) rs[i] = make_double2(0.0, 0.0);
+    double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int q = 1; q < (1 << N); ++q) {
+        const int j = __builtin_ctz(q);
+        const int g = q ^ (q >> 1);
+        const double sgn = ((g >> j) & 1) ? 1.0 : -1.0;  // column j enters or leaves
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            rs[i].x += sgn * M[i][j].x;
+            rs[i].y += sgn * M[i][j].y;
+        }
+        double2 prod = rs[0];
+#pragma unroll
+        for (int i = 1; i < N; ++i) prod = z_mul(prod, rs[i]);
+        const double sg = (__builtin_popcount(g) & 1) ? -1.0 : 1.0;
+        acc.x += sg * prod.x;
+        acc.y += sg * prod.y;
+    }
+    const double sn = (N & 1) ? -1.0 : 1.0;
+    const double re = sn * acc.x * scale, im = sn * acc.y * scale;
+    K[pair] = (float)(re * re + im * im);
+}
+
+// Whether K has too few rows (or columns) for tiles: a tile's waves take four of
+// them, and once the tiles (one per 16 along the other side) fill the chip that
+// work counts.  us, tiles / a thread per pair (n = 8: a wave per pair): n = 7, m = 10
+// 32768 long 1 row 92 / 26, 4 rows 92 / 51, 6 rows 93 / 73, 8 rows 93 / 94, 4096 long
+// 1 row 13 / 21; n = 6, m = 12 131072 long 1 row 81 / 45, 2 rows 83 / 81, 3 rows 86 / 114;
+// n = 5, m = 20 32768 long 1 row 33 / 24, 2 rows 33 / 25, 3 rows 34 / 55, 131072 long
+// (420 MB of unitaries, beyond the caches and read once per row) 2 rows 114 / 194;
+// n = 4, m = 10 131072 long 1 row 32 / 25, 2 rows 32 / 52; n = 3, m = 6 1 row 13 / 11;
+// n = 8, m = 12 32768 long 1 row 139 / 114, 2 rows 140 / 213.
+bool fid_few_rows(int m, int n, int rows, int64_t length) {
+    if (n == 8) return rows == 1;
+    if (n == 7) return rows <= 6 && length > 4096;
+    if (n < 3 || length <= 16384) return false;
+    return rows == 1 || (rows == 2 && n >= 5 && length * m * m * (int64_t)sizeof(float2) <= ((int64_t)256 << 20));
 }
 
 __global__ __launch_bounds__(kFidBlock) void fidelity_kernel(int m, int n, FidModes C, double scale,
@@ -357,7 +444,22 @@ extern "C" int fock_fidelity_kernel(int m, const int32_t* occ, const float* U1, 
     const int64_t ta = ((int64_t)B1 + T - 1) / T, tb64 = ((int64_t)B2 + T - 1) / T;
     if (n >= 1 && n <= 7 && ta * tb64 >= ((int64_t)1 << 31))
         return fail(SLOS_EUNSUPPORTED, "fock_fidelity_kernel: too many pairs");
-    if (n >= 1 && n <= 8 && ta * tb64 < ((int64_t)1 << 31)) {
+    const int64_t pair_blocks = ((int64_t)B1 * B2 + kFidBlock - 1) / kFidBlock;
+    // (a dimension of a launch holds less than 2^32 threads)
+    const bool few = fid_few_rows(m, n, std::min(B1, B2), std::max(B1, B2)) &&
+                     (n == 8 || pair_blocks * kFidBlock < ((int64_t)1 << 32));
+    if (few && n <= 7) {
+        static void* const thread_fns[5] = {(void*)&fidelity_thread_kernel<3>, (void*)&fidelity_thread_kernel<4>,
+                                            (void*)&fidelity_thread_kernel<5>, (void*)&fidelity_thread_kernel<6>,
+                                            (void*)&fidelity_thread_kernel<7>};
+        void* args[] = {(void*)&m, (void*)&C, (void*)&scale, (void*)&U1, (void*)&B1, (void*)&U2, (void*)&B2, (void*)&K};
+        hipError_t e = hipLaunchKernel(thread_fns[n - 3], dim3((unsigned)pair_blocks), dim3(kFidBlock), args, 0,
+                                       (hipStream_t)stream);
+        if (e != hipSuccess)
+            return fail(SLOS_EHIP, std::string("fock_fidelity_kernel launch: ") + hipGetErrorString(e));
+        return SLOS_OK;
+    }
+    if (n >= 1 && n <= 8 && !few && ta * tb64 < ((int64_t)1 << 31)) {
         static void* const tile_fns[8] = {(void*)&fidelity_tile_kernel<1, 0>, (void*)&fidelity_tile_kernel<2, 0>,
                                           (void*)&fidelity_tile_kernel<3, 0>, (void*)&fidelity_tile_kernel<4, 0>,
                                           (void*)&fidelity_tile_kernel<5, 0>, (void*)&fidelity_tile_kernel<6, 0>,
@@ -365,13 +467,12 @@ extern "C" int fock_fidelity_kernel(int m, const int32_t* occ, const float* U1, 
         const size_t lds = (size_t)2 * T * m * n * sizeof(double2) + (q > 0 ? (size_t)n * n * T * T * sizeof(double2) : 0);
         int tb = (int)tb64;
         unsigned tiles = (unsigned)(ta * tb64);
-        // a dimension of a launch holds less than 2^32 threads
         const unsigned gx = std::min(tiles, 1u << 23), gy = (tiles + gx - 1) / gx;
-        bool gram = U1 == U2 && B1 == B2;
+        bool gram = U1 == U2 && B1 == B2, cols = B2 < B1 && B2 < T;
         void* fn = tile_fns[n - 1];
         (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         void* args[] = {(void*)&m, (void*)&C, (void*)&scale, (void*)&U1, (void*)&B1, (void*)&U2, (void*)&B2, (void*)&K,
-                        (void*)&tb, (void*)&tiles, (void*)&gram};
+                        (void*)&tb, (void*)&tiles, (void*)&gram, (void*)&cols};
         hipError_t e = hipLaunchKernel(fn, dim3(gx, gy), dim3(T * T << q), args, lds, (hipStream_t)stream);
         if (e != hipSuccess)
             return fail(SLOS_EHIP, std::string("fock_fidelity_kernel launch: ") + hipGetErrorString(e));

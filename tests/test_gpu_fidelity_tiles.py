@@ -65,3 +65,27 @@ def test_gram_matrix_is_the_mirrored_product(n, Bn):
     iu = torch.triu_indices(Bn, Bn)
     assert torch.equal(G[iu[0], iu[1]], K[iu[0], iu[1]])
     assert (G.diagonal() - 1).abs().max().item() <= 1e-6  # complex64 unitaries: n rounding errors of 6e-8
+
+
+@pytest.mark.parametrize("n,rows,length", [(3, 1, 16385), (4, 2, 16385), (5, 2, 16400), (6, 2, 16385), (6, 1, 16385),
+                                           (7, 6, 4097), (7, 7, 4097), (8, 1, 4097), (8, 2, 100), (5, 3, 40), (2, 12, 40)])
+def test_few_rows_or_columns_against_64_bit_permanents(n, rows, length):
+    # a thread per pair, and tiles with waves that have no pairs, both ways round
+    rng = np.random.default_rng(10 * n + rows)
+    m = 8
+    U1 = W.haar_unitaries(rng, rows, m).astype(np.complex64)
+    U2 = np.tile(W.haar_unitaries(rng, 37, m), (-(-length // 37), 1, 1))[:length].astype(np.complex64)
+    occ = np.zeros(m, dtype=np.int32)
+    np.add.at(occ, rng.choice(m, size=n, replace=True), 1)
+    C = np.repeat(np.arange(m), occ)
+    fact = np.prod([float(np.prod(np.arange(1, v + 1))) for v in occ])
+    say("fidelity, few rows", n, rows, length)
+    K = B.fock_fidelity_kernel(occ, to_dev_c64(U1), to_dev_c64(U2))
+    Kt = B.fock_fidelity_kernel(occ, to_dev_c64(U2), to_dev_c64(U1))
+    assert K.shape == (rows, length) and Kt.shape == (length, rows)
+    K, Kt = K.cpu().numpy(), Kt.cpu().numpy()
+    for a in range(rows):
+        for b in (0, 1, 15, 16, 36):
+            want = abs(_perm(widen(U1[a])[:, C].conj().T @ widen(U2[b])[:, C]) / fact) ** 2
+            # U2 repeats every 37 matrices
+            assert np.abs(K[a, b::37] - want).max() <= TOL and np.abs(Kt[b::37, a] - want).max() <= TOL, (a, b)
