@@ -17,10 +17,15 @@
 // columns and of the last rows over every subset (n 2^(n-1) products each); the
 // adjoint carries (value, e-derivative) pairs through the same sums.  n = 5
 // takes 240 products where the photon recursion takes 252000 at m = 20.
-// FP64 (the sums are tiny), one wave per sample: bound by the latency of its
-// 2 n short steps.  m = 20, n = 5, B = 512: forward 11 us, adjoint 26 us; the
-// recursion with the expectation epilogue took 103 us, and the expanded weights
-// and the probability adjoint 229 us.
+// FP64 (the sums are tiny).  Bound by the latency of its n dependent levels, hence
+// a thread per column subset (a workgroup of 64 up to 6 photons, 256 for 7 and 8), and
+// four threads per matrix entry in the wide one.  One wave with loops over all
+// subsets took 44 us for a sample of 8 photons, which lost to the photon recursion
+// wherever the Fock space is small.  us, forward / adjoint, the recursion (the
+// adjoint from expanded weights) and here: m = 20, n = 5, B = 512 94 / 214 and 7.5 /
+// 13.6; m = 6, n = 8 (1287 states) B = 1 15 / 32 and 9.9 / 13.9, B = 8192 123 / 329 and
+// 70 / 121; m = 3, n = 8 (45 states) B = 1 12 / 22 and 9.7 / 14, B = 1024 13.3 / 42 and
+// 14.8 / 23; m = 2, n = 3 (4 states) B = 1 8.2 / 10.9 and 5.6 / 5.8.
 #include "slos_internal.h"
 
 namespace slos {
@@ -38,129 +43,169 @@ __device__ __forceinline__ void z_fma_conj(double2& acc, double2 a, double2 b) {
     z_fma(acc, make_double2(a.x, -a.y), b);
 }
 
-template <bool BWD>
-__global__ __launch_bounds__(64) void expect_closed_kernel(int m, BatchDev Bt, const float2* __restrict__ U,
+// Sum over the S adjacent lanes that share an entry.
+template <int S>
+__device__ __forceinline__ double2 share_sum(double2 v) {
+    for (int s = 1; s < S; s <<= 1) {
+        v.x += __shfl_xor(v.x, s, 64);
+        v.y += __shfl_xor(v.y, s, 64);
+    }
+    return v;
+}
+
+// NT threads, one per subset of the columns: 64 up to 6 photons, 256 for 7 and 8.
+template <bool BWD, int NT>
+__global__ __launch_bounds__(NT) void expect_closed_kernel(int m, BatchDev Bt, const float2* __restrict__ U,
                                                            const float* __restrict__ w, float* __restrict__ out,
                                                            float2* __restrict__ gU) {
     constexpr int H = BWD ? 2 : 1;  // values, and their e-derivatives
-    __shared__ double2 V[kMaxModes * kExpMaxN];
-    __shared__ double2 M[H][kExpMaxN * kExpMaxN];           // G and E, row a, column b
-    __shared__ double2 F[H][1 << kExpMaxN], L[H][1 << kExpMaxN];  // first rows, last rows, by column subset
-    __shared__ double2 P[H][kExpMaxN * kExpMaxN];
-    const int lane = threadIdx.x, b = blockIdx.x;
+    constexpr int S = NT / 64;      // threads that share an entry of an 8 x 8 matrix
+    // matrices and V in rows of eight: indexes by shifts
+    __shared__ double2 V[kMaxModes * 8];
+    __shared__ double2 M[H][64];          // G and E, row a, column b
+    __shared__ double2 F[H][NT], L[H][NT];  // first rows, last rows, by column subset
+    __shared__ double2 P[H][64];
+    __shared__ int mode[8];
+    const int tid = threadIdx.x;
+    const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (b >= Bt.B) return;
     const int n = ldc(Bt.n + b);
-    const float2* Ub = U + (size_t)b * m * m;
+    const float2* Ub = U + b * m * m;
     if (n == 0) {  // the vacuum: <n_j> = 0 for every U
         if (!BWD) {
-            if (lane < m) out[(size_t)b * m + lane] = 0.f;
+            if (tid < m) out[b * m + tid] = 0.f;
         } else {
-            for (int e = lane; e < m * m; e += 64) gU[(size_t)b * m * m + e] = c_zero();
+            for (int e = tid; e < m * m; e += NT) gU[b * m * m + e] = c_zero();
         }
         return;
     }
-    int mode[kExpMaxN];
-    double scale = 1.0;
-    int run = 1;
-#pragma unroll
-    for (int i = 0; i < kExpMaxN; ++i) {
-        mode[i] = i < n ? ldc(Bt.modes + (size_t)b * kMaxPhotons + i) : -1;
-        run = i > 0 && mode[i] == mode[i > 0 ? i - 1 : 0] ? run + 1 : 1;
-        if (i < n) scale /= run;
-    }
-    for (int e = lane; e < m * n; e += 64) {
-        const int j = e / n, i = e % n;
-        const float2 v = Ub[j * m + ldg(Bt.modes + (size_t)b * kMaxPhotons + i)];
-        V[e] = make_double2(v.x, v.y);
-    }
-    __syncthreads();
-    if (lane < n * n) {
-        const int a = lane / n, c = lane % n;
-        double2 g = make_double2(0.0, 0.0), e = g;
-        for (int j = 0; j < m; ++j) {
-            double2 t = make_double2(0.0, 0.0);
-            z_fma_conj(t, V[j * n + a], V[j * n + c]);
-            g.x += t.x;
-            g.y += t.y;
-            if (BWD) {
-                const double wj = w[(size_t)b * m + j];
-                e.x = fma(wj, t.x, e.x);
-                e.y = fma(wj, t.y, e.y);
-            }
+    {
+        const int i = tid & 7;
+        const int mi = ldg(Bt.modes + b * kMaxPhotons + i);
+        if (tid < 8) mode[i] = i < n ? mi : -1;
+        for (int j = tid >> 3; j < m; j += NT / 8) {
+            const float2 v = i < n ? Ub[j * m + mi] : c_zero();
+            V[8 * j + i] = make_double2(v.x, v.y);
         }
-        M[0][lane] = g;
-        if (BWD) M[H - 1][lane] = e;
     }
-    if (lane == 0) {
+    if (tid == 0) {
         F[0][0] = L[0][0] = make_double2(1.0, 0.0);
         if (BWD) F[H - 1][0] = L[H - 1][0] = make_double2(0.0, 0.0);
     }
     __syncthreads();
-    const int full = (1 << n) - 1;
+    double scale = 1.0;
+    for (int i = 1, run = 1; i < n; ++i) {
+        run = mode[i] == mode[i - 1] ? run + 1 : 1;
+        scale /= run;
+    }
+    // entry (a, c) of the matrices, share q of its sums
+    const int a = tid / (8 * S), c = tid / S & 7, q = tid % S;
+    {
+        double2 g = make_double2(0.0, 0.0), e = g;
+#pragma unroll 4
+        for (int j = q; j < m; j += S) {
+            double2 t = make_double2(0.0, 0.0);
+            z_fma_conj(t, V[8 * j + a], V[8 * j + c]);
+            g.x += t.x;
+            g.y += t.y;
+            if (BWD) {
+                const double wj = w[b * m + j];
+                e.x = fma(wj, t.x, e.x);
+                e.y = fma(wj, t.y, e.y);
+            }
+        }
+        g = share_sum<S>(g);
+        if (BWD) e = share_sum<S>(e);
+        if (q == 0) {
+            M[0][8 * a + c] = g;
+            if (BWD) M[H - 1][8 * a + c] = e;
+        }
+    }
+    __syncthreads();
+    const int full = (1 << n) - 1, size = tid <= full ? __builtin_popcount(tid) : 0;
     for (int l = 1; l < n; ++l) {  // minors leave one row out: subsets of up to n-1 columns
-        const int rf = (l - 1) * n, rl = (n - l) * n;
-        for (int s = lane; s <= full; s += 64) {
-            if (__builtin_popcount(s) != l) continue;
-            double2 f = make_double2(0.0, 0.0), fe = f, q = f, qe = f;
-            for (int i = 0; i < n; ++i) {
-                if (!((s >> i) & 1)) continue;
-                const int r = s & ~(1 << i);
+        if (size == l) {
+            const int rf = 8 * (l - 1), rl = 8 * (n - l);
+            double2 f = make_double2(0.0, 0.0), fe = f, p = f, pe = f;
+            for (int left = tid; left != 0; left &= left - 1) {
+                const int i = __builtin_ctz(left), r = tid & ~(1 << i);
                 z_fma(f, M[0][rf + i], F[0][r]);
-                z_fma(q, M[0][rl + i], L[0][r]);
+                z_fma(p, M[0][rl + i], L[0][r]);
                 if (BWD) {
                     z_fma(fe, M[0][rf + i], F[H - 1][r]);
                     z_fma(fe, M[H - 1][rf + i], F[0][r]);
-                    z_fma(qe, M[0][rl + i], L[H - 1][r]);
-                    z_fma(qe, M[H - 1][rl + i], L[0][r]);
+                    z_fma(pe, M[0][rl + i], L[H - 1][r]);
+                    z_fma(pe, M[H - 1][rl + i], L[0][r]);
                 }
             }
-            F[0][s] = f;
-            L[0][s] = q;
+            F[0][tid] = f;
+            L[0][tid] = p;
             if (BWD) {
-                F[H - 1][s] = fe;
-                L[H - 1][s] = qe;
+                F[H - 1][tid] = fe;
+                L[H - 1][tid] = pe;
             }
         }
         __syncthreads();
     }
-    if (lane < n * n) {  // rows before a take the columns s, rows after it the rest but column c
-        const int a = lane / n, c = lane % n;
+    {  // rows before a take the columns s, rows after it the rest but column c: the
+       // n-1 other columns' subsets r of size a
         double2 p = make_double2(0.0, 0.0), d = p;
-        for (int s = 0; s <= full; ++s) {
-            if (__builtin_popcount(s) != a || ((s >> c) & 1)) continue;
-            const int r = full & ~s & ~(1 << c);
-            z_fma(p, F[0][s], L[0][r]);
-            if (BWD) {
-                z_fma(d, F[0][s], L[H - 1][r]);
-                z_fma(d, F[H - 1][s], L[0][r]);
-            }
-        }
-        P[0][lane] = p;
-        if (BWD) P[H - 1][lane] = d;
-    }
-    __syncthreads();
-    if constexpr (!BWD) {
-        if (lane < m) {
-            double v = 0.0;
-            for (int a = 0; a < n; ++a) {
-                double2 t = make_double2(0.0, 0.0);
-                for (int c = 0; c < n; ++c) z_fma(t, P[0][a * n + c], V[lane * n + c]);
-                v += V[lane * n + a].x * t.x + V[lane * n + a].y * t.y;
-            }
-            out[(size_t)b * m + lane] = (float)(scale * v);
-        }
-    } else {
-        for (int e = lane; e < m * m; e += 64) {
-            const int j = e / m, col = e % m;
-            const double wj = w[(size_t)b * m + j];
-            double2 g = make_double2(0.0, 0.0);
-            for (int a = 0; a < n; ++a) {
-                if (ldg(Bt.modes + (size_t)b * kMaxPhotons + a) != col) continue;
-                for (int c = 0; c < n; ++c) {
-                    const double2 p = P[0][a * n + c], d = P[H - 1][a * n + c];
-                    z_fma(g, make_double2(fma(wj, p.x, d.x), fma(wj, p.y, d.y)), V[j * n + c]);
+        if (a < n && c < n) {
+#pragma unroll 4
+            for (int r = q; r < 1 << (n - 1); r += S) {
+                if (__builtin_popcount(r) != a) continue;
+                const int s = (r & ((1 << c) - 1)) | (r >> c) << (c + 1), rest = full & ~s & ~(1 << c);
+                z_fma(p, F[0][s], L[0][rest]);
+                if (BWD) {
+                    z_fma(d, F[0][s], L[H - 1][rest]);
+                    z_fma(d, F[H - 1][s], L[0][rest]);
                 }
             }
-            gU[(size_t)b * m * m + e] = make_float2((float)(2.0 * scale * g.x), (float)(2.0 * scale * g.y));
+        }
+        p = share_sum<S>(p);
+        if (BWD) d = share_sum<S>(d);
+        if (q == 0) {
+            P[0][8 * a + c] = p;
+            if (BWD) P[H - 1][8 * a + c] = d;
+        }
+    }
+    __syncthreads();
+    // thread (j, row): row of P V for mode j
+    const int row = tid & 7;
+    for (int j0 = 0; j0 < m; j0 += NT / 8) {
+        const int j = j0 + (tid >> 3);
+        double2 t = make_double2(0.0, 0.0);
+        if (j < m && row < n) {
+            const double wj = BWD ? w[b * m + j] : 0.0;
+            for (int i = 0; i < n; ++i) {
+                const double2 p = P[0][8 * row + i];
+                if (BWD) {
+                    const double2 d = P[H - 1][8 * row + i];
+                    z_fma(t, make_double2(fma(wj, p.x, d.x), fma(wj, p.y, d.y)), V[8 * j + i]);
+                } else {
+                    z_fma(t, p, V[8 * j + i]);
+                }
+            }
+        }
+        if constexpr (!BWD) {
+            double v = j < m && row < n ? V[8 * j + row].x * t.x + V[8 * j + row].y * t.y : 0.0;
+            for (int s = 1; s < 8; s <<= 1) v += __shfl_xor(v, s, 64);
+            if (j < m && row == 0) out[b * m + j] = (float)(scale * v);
+        } else {
+            __syncthreads();  // gradients of NT / 8 modes at a time through F
+            F[0][tid] = t;
+            __syncthreads();
+            const int rows = min(m - j0, NT / 8);
+            for (int e = tid; e < rows * m; e += NT) {
+                const int jj = e / m, col = e % m;
+                double2 g = make_double2(0.0, 0.0);
+                for (int i = 0; i < n; ++i)
+                    if (mode[i] == col) {
+                        g.x += F[0][8 * jj + i].x;
+                        g.y += F[0][8 * jj + i].y;
+                    }
+                gU[b * m * m + (int64_t)j0 * m + e] = make_float2((float)(2.0 * scale * g.x), (float)(2.0 * scale * g.y));
+            }
         }
     }
 }
@@ -173,9 +218,13 @@ bool expect_closed_ok(const slos_batch_s& Bt) { return !restricted_plan(*Bt.plan
 
 int launch_expect_closed(const slos_batch_s& Bt, bool bwd, const float2* U, const float* w, float* out, float2* gU,
                          hipStream_t stream) {
-    void* fn = bwd ? (void*)&expect_closed_kernel<true> : (void*)&expect_closed_kernel<false>;
+    const bool wide = Bt.n_max > 6;
+    void* fn = bwd ? (wide ? (void*)&expect_closed_kernel<true, 256> : (void*)&expect_closed_kernel<true, 64>)
+                   : (wide ? (void*)&expect_closed_kernel<false, 256> : (void*)&expect_closed_kernel<false, 64>);
     void* args[] = {(void*)&Bt.plan->m, (void*)&Bt.dev, (void*)&U, (void*)&w, (void*)&out, (void*)&gU};
-    hipError_t e = hipLaunchKernel(fn, dim3((unsigned)Bt.B), dim3(64), args, 0, stream);
+    // (a dimension of a launch holds less than 2^32 threads)
+    const unsigned gx = std::min((unsigned)Bt.B, 1u << 22), gy = ((unsigned)Bt.B + gx - 1) / gx;
+    hipError_t e = hipLaunchKernel(fn, dim3(gx, gy), dim3(wide ? 256 : 64), args, 0, stream);
     if (e != hipSuccess) return fail(SLOS_EHIP, std::string("expectation launch: ") + hipGetErrorString(e));
     return SLOS_OK;
 }

@@ -54,3 +54,31 @@ def test_photon_numbers_beyond_take_the_recursion():
     e = B.fock_mode_expectations(batch, to_dev_c64(U)).cpu().numpy()
     for b in range(2):
         assert np.abs(e[b] - O.mode_expectations(widen(U[b]), occ[b])).max() <= 2e-5
+
+
+@pytest.mark.parametrize("m,n", [(32, 3), (9, 6), (9, 7), (6, 8), (1, 8), (17, 4), (8, 1)])
+def test_every_photon_number_below_in_one_batch(m, n):
+    # one thread per column subset, 64 of them up to 6 photons and 256 above: samples
+    # of every photon number up to n at both widths, modes up to and past a
+    # workgroup's rows of eight
+    rng = np.random.default_rng(5 * m + n)
+    occ = np.zeros((n + 1, m), dtype=np.int32)
+    for b in range(n + 1):
+        np.add.at(occ[b], rng.choice(m, size=b, replace=True), 1)
+    U = (W.haar_unitaries(rng, n + 1, m) * 1.05).astype(np.complex64)
+    say("expectations, photon numbers up to", n, "modes", m)
+    batch = B.Batch(B.Plan(m, n), occ)
+    w = rng.standard_normal((n + 1, m)).astype(np.float32)
+    Ud = to_dev_c64(U)
+    e = B.fock_mode_expectations(batch, Ud).cpu().numpy()
+    g = B.fock_mode_expectations_backward(batch, Ud, torch.from_numpy(w).to(Ud.device)).cpu().numpy()
+    for b in range(n + 1):
+        ref = O.mode_expectations(widen(U[b]), occ[b])
+        # FP64 sums rounded once
+        assert np.abs(e[b] - ref).max() <= 2.0 ** -23 * max(1.0, np.abs(ref).max())
+        if b == 0:
+            assert not g[b].any()
+            continue
+        basis = O.fock_basis(m, b)
+        ref_g = O.probs_grad(widen(U[b]), occ[b], np.asarray(basis) @ w[b].astype(np.float64))
+        assert rel_err(g[b], ref_g) <= 2.0 ** -23
