@@ -254,14 +254,14 @@ __global__ __launch_bounds__(kMeasureBlock) void sample_kernel(BatchDev Bt, cons
 // write and the search reads back are 8 bytes a state.  m = 20, n = 5, B = 512,
 // S = 1024: 34 us (39 with one run of loads in flight per thread); the three passes that form the sums in memory took 165.
 constexpr int kRun = 16;
-constexpr int kDirectBlock = 1024;
 constexpr int64_t kDirectStates = (int64_t)kRun * 8192;  // run sums within 64 KB of LDS
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
-__global__ __launch_bounds__(kDirectBlock) void sample_direct_kernel(BatchDev Bt, const float* __restrict__ p,
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void sample_direct_kernel(BatchDev Bt, const float* __restrict__ p,
                                                                      const float* __restrict__ u, int S, int parts,
                                                                      unsigned groups, int32_t* __restrict__ shots) {
-    constexpr int kWaves = kDirectBlock / 64;
+    constexpr int kWaves = BLOCK / 64;
     extern __shared__ double runs[];  // [R]: cumulative sums at the runs' ends
     __shared__ double wtot[kWaves];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -274,19 +274,19 @@ __global__ __launch_bounds__(kDirectBlock) void sample_direct_kernel(BatchDev Bt
     const int R = (N + kRun - 1) / kRun;
     const int whole = N / kRun;  // runs without an end inside
     constexpr int V = 3;         // runs per thread in flight
-    for (int r0 = tid; r0 < whole; r0 += kDirectBlock * V) {
+    for (int r0 = tid; r0 < whole; r0 += BLOCK * V) {
         f4u x[V][kRun / 4];
 #pragma unroll
         for (int q = 0; q < V; ++q)
 #pragma unroll
             for (int i = 0; i < kRun / 4; ++i)
-                x[q][i] = *(const f4u*)(pb + min(r0 + q * kDirectBlock, whole - 1) * kRun + 4 * i);
+                x[q][i] = *(const f4u*)(pb + min(r0 + q * BLOCK, whole - 1) * kRun + 4 * i);
 #pragma unroll
         for (int q = 0; q < V; ++q) {
             double v = 0.0;
 #pragma unroll
             for (int i = 0; i < kRun; ++i) v += (double)x[q][i / 4][i % 4];
-            if (r0 + q * kDirectBlock < whole) runs[r0 + q * kDirectBlock] = v;
+            if (r0 + q * BLOCK < whole) runs[r0 + q * BLOCK] = v;
         }
     }
     if (tid == 0 && whole < R) {
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(kDirectBlock) void sample_direct_kernel(BatchDev Bt
     }
     __syncthreads();
     // inclusive scan: each thread its own stretch, then over the threads
-    const int each = (R + kDirectBlock - 1) / kDirectBlock;
+    const int each = (R + BLOCK - 1) / BLOCK;
     const int lo = min(tid * each, R), hi = min(lo + each, R);
     double x = 0.0;
     for (int r = lo; r < hi; ++r) x += runs[r];
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(kDirectBlock) void sample_direct_kernel(BatchDev Bt
     }
     __syncthreads();
     const double total = runs[R - 1];
-    for (int i = part * kDirectBlock + tid; i < S; i += parts * kDirectBlock) {
+    for (int i = part * BLOCK + tid; i < S; i += parts * BLOCK) {
         const double target = (double)u[(int64_t)b * S + i] * total;
         int a = 0, e = R - 1;  // the first run that ends above the target, the last if none does
         while (a < e) {
@@ -324,11 +324,23 @@ __global__ __launch_bounds__(kDirectBlock) void sample_direct_kernel(BatchDev Bt
             else a = mid + 1;
         }
         double c = a > 0 ? runs[a - 1] : 0.0;
-        const int t1 = min((a + 1) * kRun, N) - 1;
         int t = a * kRun;
-        for (; t < t1; ++t) {
-            c += (double)pb[t];
-            if (c > target) break;
+        const int rest = N - 1 - t;  // states of the run after its first, if it is the last
+        f4u x[kRun / 4] = {};        // the run in one round of loads
+        if (a < whole) {
+#pragma unroll
+            for (int q = 0; q < kRun / 4; ++q) x[q] = *(const f4u*)(pb + t + 4 * q);
+        } else {
+#pragma unroll
+            for (int q = 0; q < kRun; ++q)
+                if (q < rest) x[q / 4][q % 4] = pb[t + q];
+        }
+        bool above = false;
+#pragma unroll
+        for (int q = 0; q < kRun - 1; ++q) {
+            c += (double)x[q / 4][q % 4];
+            above |= c > target;
+            t += !above && q < rest;
         }
         shots[(int64_t)b * S + i] = t;
     }
@@ -477,6 +489,17 @@ int launch_threshold(const void* fn, int C, const slos_batch_s& Bt, const float*
     return SLOS_OK;
 }
 
+// Threads per sample of the direct kernel: 1024 sum a sample soonest and search
+// for many shots at once; where samples are many and short, eight workgroups of 256
+// per CU do more of them.  us of the whole call with three passes, at 256 and at 1024
+// threads: 10 states, 4096 samples, 1 shot each 21 / 18 / 42, 65536 samples 230 / 211 /
+// 610; 56 states, 20000 samples, 256 shots 135 / 113 / 251; 715 states, 4096 samples, 2048
+// shots 134 / 87 / 124, but 512 samples 31 / 29 / 19; 12376 states, 2048 samples, 2048
+// shots 466 / 157 / 139.
+int direct_block(const slos_batch_s& Bt) {
+    return Bt.B >= 4 * Bt.plan->num_cu && Bt.plan->N[Bt.n_max] <= 8192 ? 256 : 1024;
+}
+
 }  // namespace
 
 int launch_threshold_gather(const slos_batch_s& Bt, const float* p, float* out, hipStream_t stream) {
@@ -492,17 +515,19 @@ int launch_sample(const slos_batch_s& Bt, const float* p, double* part, double* 
     const int64_t Nmax = Bt.plan->N[Bt.n_max];
     if (Nmax <= kDirectStates) {
         if (S == 0) return SLOS_OK;
+        const int block = direct_block(Bt);
         // a workgroup per sample, more where samples alone leave CUs idle (each
         // then sums its sample again), never with fewer shots than threads
         const int64_t fill = std::max<int64_t>(1, 2 * (int64_t)std::max(Bt.plan->num_cu, 1) / Bt.B);
-        int parts = (int)std::min<int64_t>(fill, ((int64_t)S + kDirectBlock - 1) / kDirectBlock);
+        int parts = (int)std::min<int64_t>(fill, ((int64_t)S + block - 1) / block);
         const size_t lds = (size_t)((Nmax + kRun - 1) / kRun) * sizeof(double);
-        (void)hipFuncSetAttribute((void*)&sample_direct_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        void* fn = block == 256 ? (void*)&sample_direct_kernel<256> : (void*)&sample_direct_kernel<1024>;
+        (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         // a dimension of a launch holds less than 2^32 threads
         unsigned groups = (unsigned)Bt.B * (unsigned)parts;
         const unsigned gx = std::min(groups, 1u << 21), gy = (groups + gx - 1) / gx;
         void* args[] = {(void*)&Bt.dev, (void*)&p, (void*)&u, (void*)&S, (void*)&parts, (void*)&groups, (void*)&shots};
-        hipError_t e = hipLaunchKernel((void*)&sample_direct_kernel, dim3(gx, gy), dim3(kDirectBlock), args, lds, stream);
+        hipError_t e = hipLaunchKernel(fn, dim3(gx, gy), dim3(block), args, lds, stream);
         if (e != hipSuccess) return fail(SLOS_EHIP, std::string("fock_sample launch: ") + hipGetErrorString(e));
         return SLOS_OK;
     }
