@@ -39,7 +39,7 @@ constexpr int kDenseBlock = 128;
 // LDS plan of an n-photon input (bytes).
 struct DenseLayout {
     uint32_t T[kMaxPhotons + 1];     // T_k, float2 [N_k][N_{n-k}]
-    uint32_t g[2];                   // gT of the step and of the one above, double2 (backward)
+    uint32_t g[2], gn;               // gT_k at g[k & 1] for k < n, and gT_n, double2 (backward)
     uint32_t U;                      // float2 [m][m]
     uint32_t part;                   // float2 [kDenseBlock]: partial sums of gU (backward)
     uint32_t succ[kMaxPhotons + 1];  // uint16 [N_{l-1}][m], l = 1..n: rank of I' + e_i
@@ -47,18 +47,23 @@ struct DenseLayout {
     uint32_t bytes;
 };
 __host__ __device__ inline void dense_layout(const int* N, int m, int n, bool bwd, DenseLayout& L) {
-    uint32_t at = 0;
-    uint32_t most = 0;
+    uint32_t at = 0, most[2] = {0, 0};  // largest T_k, k < n, of each parity
     for (int k = 0; k <= n; ++k) {
         L.T[k] = at;
         const uint32_t b = 8u * (uint32_t)N[k] * (uint32_t)N[n - k];
+        if (k < n) most[k & 1] = b > most[k & 1] ? b : most[k & 1];
         if (k < n || !bwd) at += b;  // the adjoint starts from the given gradient, not from T_n
-        most = b > most ? b : most;
     }
-    if (bwd) at = (at + 15u) & ~15u;
-    L.g[0] = at;
-    L.g[1] = at + (bwd ? 2 * most : 0);
-    at += bwd ? 4 * most : 0;
+    if (bwd) {
+        // gT_{n-2}, gT_{n-4}, .. are formed when T_{n-1} and gT_n have been read: over both
+        L.T[n - 1] = (L.T[n - 1] + 15u) & ~15u;
+        L.g[n & 1] = L.T[n - 1];
+        L.gn = (L.T[n - 1] + 8u * (uint32_t)N[n - 1] * (uint32_t)N[1] + 15u) & ~15u;
+        const uint32_t over = L.g[n & 1] + 2 * most[n & 1], end = L.gn + 16u * (uint32_t)N[n];
+        at = ((over > end ? over : end) + 15u) & ~15u;
+        L.g[(n - 1) & 1] = at;
+        at += 2 * most[(n - 1) & 1];
+    }
     L.U = at;
     at += 8u * (uint32_t)(m * m);
     L.part = at;
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
         for (int t = tid; t < N[n]; t += kDenseBlock)
             A.y[o0 + t] = n > 0 ? c_scale(Tn[t], 1.f / ldg(nrm + t)) : Tn[t];
     } else {
-        double2* gn = (double2*)(dlds + L.g[n & 1]);  // gT_k at g[k & 1]
+        double2* gn = (double2*)(dlds + L.gn);
         const uint16_t* predn = (const uint16_t*)(dlds + L.pred[n]);
         for (int t = tid; t < N[n]; t += kDenseBlock) {
             const float2 v = A.gy[o0 + t];
@@ -182,7 +187,7 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
         for (auto& v : gu) v = c_zero();
         for (int k = n - 1; k >= 0; --k) {
             const float2* Tk = (const float2*)(dlds + L.T[k]);
-            const double2* gu1 = (const double2*)(dlds + L.g[(k + 1) & 1]);
+            const double2* gu1 = (const double2*)(dlds + (k + 1 == n ? L.gn : L.g[(k + 1) & 1]));
             double2* gk = (double2*)(dlds + L.g[k & 1]);
             const uint16_t* succI = (const uint16_t*)(dlds + L.succ[n - k]);
             const uint16_t* succJ = (const uint16_t*)(dlds + L.succ[k + 1]);
@@ -265,8 +270,8 @@ size_t dense_lds(const slos_plan_s& P, int n, bool bwd) {
 
 // The rule, per group: one input of `comps` distinct components of n photons
 // goes through the steps above where they take no more products than one
-// simulation per component, and its adjoint fits in 88 KB of LDS (most take
-// half of that or less: two workgroups a CU or more).  At the line the steps already win, their cost being
+// simulation per component, and its adjoint fits in 80 KB of LDS (two workgroups
+// a CU; most take half of that or less).  At the line the steps already win, their cost being
 // latency (us, forward / adjoint, steps against components): m = 6, n = 3, 9 of
 // 56 states, 1024 inputs 9.9 / 21 against 38 / 177; m = 4, n = 2, 5 of 10 states,
 // 256 inputs 14.5 / 14.7 (a call's cost on the host) against 18.7 / 33; m = 8,
@@ -281,7 +286,7 @@ bool dense_superposition_ok(const slos_plan_s& P, int n, int64_t comps) {
         steps += P.N[k] * P.N[n - k] * P.m;
         single += k * P.N[k];
     }
-    return steps <= single * comps && dense_lds(P, n, true) <= 88 * 1024;
+    return steps <= single * comps && dense_lds(P, n, true) <= 80 * 1024;
 }
 
 int launch_dense_superposition(const SupDev& S, const slos_batch_s& Bt, bool bwd, const float2* U, const float2* x,
