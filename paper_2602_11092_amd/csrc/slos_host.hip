@@ -1072,7 +1072,7 @@ size_t sup_ws_parts(const slos_superposition_s& S, bool bwd, size_t* uc, size_t*
 // components' op (which runs one simulation per component).
 bool dense_steps(const slos_superposition_s& S, int op) {
     const Config& c = S.batch->cfg[op];
-    return S.dev.dense && c.variant == SLOS_VARIANT_AUTO && c.block == 0;
+    return (op_backward(op) ? S.dev.dense_bwd : S.dev.dense_fwd) && c.variant == SLOS_VARIANT_AUTO && c.block == 0;
 }
 
 }  // namespace
@@ -1119,11 +1119,12 @@ extern "C" int slos_superposition_create(slos_batch_t components, int G, const i
         return fail(SLOS_EUNSUPPORTED, "slos_superposition_create: too many components for one launch");
     }
     // dense inputs: every group has enough distinct components for the
-    // photon-by-photon steps to take fewer products than one simulation each
+    // photon-by-photon steps to take fewer products than one simulation each;
+    // a direction takes them if each group's are sooner done
     std::vector<int32_t> crank(std::max(Bt.B, 1), 0);
     std::vector<float> cnorm(std::max(Bt.B, 1), 1.f);
     std::vector<uint32_t> gcols(std::max(G, 1), 0u);
-    bool dense = G > 0;
+    bool dense = G > 0, sooner[2] = {true, true};
     std::vector<Counter> ranks;
     std::vector<char> seen;
     for (int n = 0; n <= Bt.n_max && dense; ++n) ranks.emplace_back(Bt.plan->m, n);
@@ -1132,6 +1133,8 @@ extern "C" int slos_superposition_create(slos_batch_t components, int G, const i
         const int n = Bt.n_host[c0];
         dense = c1 - c0 <= Bt.plan->N[n] && dense_superposition_ok(*Bt.plan, n, c1 - c0);
         if (!dense) break;
+        for (int d = 0; d < 2; ++d)
+            sooner[d] = sooner[d] && dense_superposition_sooner(*Bt.plan, n, c1 - c0, G, Bt.B, d == 1);
         S->dev.n_present |= 1u << n;
         const Counter& C = ranks[n];
         seen.assign((size_t)Bt.plan->N[n], 0);
@@ -1149,7 +1152,8 @@ extern "C" int slos_superposition_create(slos_batch_t components, int G, const i
             if (seen[crank[c]]++) dense = false;  // repeated states: summed component by component
         }
     }
-    S->dev.dense = dense;
+    S->dev.dense_fwd = dense && sooner[0];
+    S->dev.dense_bwd = dense && sooner[1];
     const size_t o_grp = 0, o_goff = align256((size_t)std::max(Bt.B, 1) * 4), o_ooff = o_goff + align256((G + 1) * 8);
     const size_t o_cr = o_ooff + align256((G + 1) * 8), o_cn = o_cr + align256(crank.size() * 4);
     const size_t o_gc = o_cn + align256(cnorm.size() * 4);

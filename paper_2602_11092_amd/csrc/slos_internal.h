@@ -221,8 +221,8 @@ struct SupDev {
     const int64_t* goff = nullptr;   // [G+1]
     const int64_t* ooff = nullptr;   // [G+1]
     int64_t max_n_states = 1;        // largest output block of a group
-    // dense inputs (slos_superpose.hip): set where every group qualifies
-    bool dense = false;
+    // dense inputs (slos_superpose.hip): the directions that take the steps
+    bool dense_fwd = false, dense_bwd = false;
     uint32_t n_present = 0;          // bit n: some group holds n photons
     const int32_t* crank = nullptr;  // [C] basis rank of each component's state
     const float* cnorm = nullptr;    // [C] sqrt(prod s!)
@@ -234,6 +234,10 @@ int launch_superposition(int kind, const SupDev& S, const slos_batch_s& Bt, cons
 // ---- dense superpositions: slos_superpose.hip ----
 // whether an input of `comps` distinct n-photon components takes the dense steps
 bool dense_superposition_ok(const slos_plan_s& P, int n, int64_t comps);
+// whether that is sooner done than one simulation per component, beside `inputs` inputs
+// of all_comps components in all
+bool dense_superposition_sooner(const slos_plan_s& P, int n, int64_t comps, int64_t inputs, int64_t all_comps,
+                                bool bwd);
 // forward: out = the groups' amplitudes; backward: out = dL/dU, gx = dL/dx or nullptr
 int launch_dense_superposition(const SupDev& S, const slos_batch_s& Bt, bool bwd, const float2* U, const float2* x,
                                const float2* gy, float2* out, float2* gx, hipStream_t stream);

@@ -268,16 +268,11 @@ size_t dense_lds(const slos_plan_s& P, int n, bool bwd) {
 
 }  // namespace
 
-// The rule, per group: one input of `comps` distinct components of n photons
-// goes through the steps above where they take no more products than one
-// simulation per component, and its adjoint fits in 80 KB of LDS (two workgroups
-// a CU; most take half of that or less).  At the line the steps already win, their cost being
-// latency (us, forward / adjoint, steps against components): m = 6, n = 3, 9 of
-// 56 states, 1024 inputs 9.9 / 21 against 38 / 177; m = 4, n = 2, 5 of 10 states,
-// 256 inputs 14.5 / 14.7 (a call's cost on the host) against 18.7 / 33; m = 8,
-// n = 4, 40 of 330 states, 256 inputs 31 / 112 against 90 / 286.  Below it the
-// component route is kept, as its results for a single component are those of
-// the plain amplitudes bit for bit.
+// Whether an input of `comps` distinct components of n photons can go through
+// the steps above: they take no more products than one simulation per component
+// (below that the component route is kept, as its results for a single component
+// are those of the plain amplitudes bit for bit), and the adjoint fits in 80 KB of
+// LDS (two workgroups a CU; most take half of that or less).
 bool dense_superposition_ok(const slos_plan_s& P, int n, int64_t comps) {
     if (restricted_plan(P) || (P.flags & SLOS_PLAN_FORWARD_ONLY) || n < 1) return false;
     int64_t steps = 0, single = 0;
@@ -287,6 +282,36 @@ bool dense_superposition_ok(const slos_plan_s& P, int n, int64_t comps) {
         single += k * P.N[k];
     }
     return steps <= single * comps && dense_lds(P, n, true) <= 80 * 1024;
+}
+
+// Whether the steps are also sooner done.  They take one workgroup per input, so
+// their time is that of one input's chain of steps until the inputs fill the chip
+// twice over; one simulation per component spreads its components over the chip,
+// and walks an input's components one after another only to combine them.  Both
+// fitted, us, to measurements at 19 spaces (1 to 256 inputs, the fewest
+// components and all of them): the adjoint's chain 4 + 4 n + (0.7 + 0.65 n) per 1000
+// products, the forward's a 3.6th; one simulation per component 12 + 1.5 n + 0.055 m^2,
+// 0.23 per component of an input and 0.022 or more per component beyond 512 (without
+// dL/dx, as in training with fixed inputs), the forward 11, 0.5 and 0.006.  Either side
+// of the line, steps / components: adjoint m = 8, n = 4, 17 of 330 states, 16 inputs 115
+// / 35, 256 inputs 115 / 133, all states, 4 inputs 115 / 142; m = 6, n = 4, 11 of 126, 1
+// input 45 / 30, all 45 / 59; m = 3, n = 8, all 45, 16 inputs 57 / 56, 64 inputs 56 / 133;
+// m = 6, n = 3, all 56, 1 input 18 / 38; forward m = 6, n = 5, 13 of 252, 16 inputs 29 / 17,
+// m = 8, n = 4, 41 of 330, 1 input 29 / 41.
+bool dense_superposition_sooner(const slos_plan_s& P, int n, int64_t comps, int64_t inputs, int64_t all_comps,
+                                bool bwd) {
+    double steps = 0, single = 0;
+    for (int k = 1; k <= n; ++k) {
+        steps += (double)P.N[k] * P.N[n - k] * P.m;
+        single += (double)k * P.N[k];
+    }
+    const double mm = (double)P.m * P.m, beyond = (double)std::max<int64_t>(0, all_comps - 512);
+    const int64_t at_once = std::max(P.num_cu, 1) * (int64_t)(160 * 1024 / dense_lds(P, n, bwd));
+    const double rounds = (double)((inputs + at_once - 1) / at_once);
+    const double chain = (4.0 + 4.0 * n + steps * (0.7 + 0.65 * n) * 1e-3) * rounds;
+    if (!bwd) return chain / 3.6 <= 11.0 + 0.5 * comps + 0.006 * beyond;
+    const double each = std::max(0.022, std::max(0.012e-3 * single, 0.9e-4 * mm));
+    return chain <= 12.0 + 1.5 * n + 0.055 * mm + 0.23 * comps + each * beyond;
 }
 
 int launch_dense_superposition(const SupDev& S, const slos_batch_s& Bt, bool bwd, const float2* U, const float2* x,

@@ -99,21 +99,77 @@ def test_columns_no_component_uses_are_not_read():
     assert torch.isfinite(torch.view_as_real(gU)).all() and torch.count_nonzero(gU[:, :, 2]) == 0
 
 
-@pytest.mark.parametrize("m,n", [(4, 2), (6, 3), (8, 3), (5, 4), (3, 6), (2, 9), (14, 3)])
-def test_grad_x_is_rounded_once(m, n):
+# (as many inputs as it takes for the steps to be chosen)
+@pytest.mark.parametrize("m,n,G", [(4, 2, 1), (6, 3, 1), (8, 3, 1), (5, 4, 1), (3, 6, 64), (2, 9, 512), (14, 3, 4)])
+def test_grad_x_is_rounded_once(m, n, G):
     # dL/dx_c = sum_t conj(a_c[t]) dL/dy_t, linear in float32 data: carried in 64
     # bits, each part is off by its own rounding to float32, 2^-24 of it at most
     rng = np.random.default_rng(10 * m + n)
-    occ = np.asarray(O.fock_basis(m, n), dtype=np.int32)
-    N = len(occ)
-    say("dL/dx of dense inputs", m, n)
-    U = W.haar_unitaries(rng, 1, m).astype(np.complex64)
-    x = (rng.standard_normal(N) + 1j * rng.standard_normal(N)).astype(np.complex64) / np.float32(np.sqrt(2 * N))
-    gy = (rng.standard_normal(N) + 1j * rng.standard_normal(N)).astype(np.complex64)
-    batch = B.Batch(B.Plan(m, n), occ)
-    sup = B.Superposition(batch, [0, N])
+    basis = np.asarray(O.fock_basis(m, n), dtype=np.int32)
+    N = len(basis)
+    say("dL/dx of dense inputs", m, n, G)
+    U = W.haar_unitaries(rng, G, m).astype(np.complex64)
+    x = (rng.standard_normal(G * N) + 1j * rng.standard_normal(G * N)).astype(np.complex64) / np.float32(np.sqrt(2 * N))
+    gy = (rng.standard_normal(G * N) + 1j * rng.standard_normal(G * N)).astype(np.complex64)
+    batch = B.Batch(B.Plan(m, n), np.tile(basis, (G, 1)))
+    sup = B.Superposition(batch, np.arange(G + 1) * N)
     _, gx = B.fock_superposition_amplitudes_backward(sup, to_dev_c64(U), torch.from_numpy(x).to(DEV),
                                                      torch.from_numpy(gy).to(DEV))
+    gx = gx.cpu().numpy().reshape(G, N)
+    gy = gy.astype(np.complex128).reshape(G, N)
     few = rng.permutation(N)[:64]
-    ref = np.array([np.vdot(O.amplitudes(widen(U[0]), occ[c]), gy.astype(np.complex128)) for c in few])
-    assert rel_err(gx.cpu().numpy()[few], ref) <= 2.0 ** -24 + 1e-12
+    for g in sorted({0, G - 1}):
+        ref = np.array([np.vdot(O.amplitudes(widen(U[g]), basis[c]), gy[g]) for c in few])
+        assert rel_err(gx[g, few], ref) <= 2.0 ** -24 + 1e-12
+
+
+@pytest.mark.parametrize("m,n,comps,G,steps", [(8, 4, 17, 16, False), (8, 4, 17, 512, True), (8, 4, 330, 4, True),
+                                               (6, 4, 11, 1, False), (6, 4, 126, 1, True)])
+def test_adjoint_takes_the_steps_where_they_are_sooner(m, n, comps, G, steps):
+    rng = np.random.default_rng(m + comps)
+    occ = np.tile(np.asarray(O.fock_basis(m, n), dtype=np.int32)[:comps], (G, 1))
+    batch = B.Batch(B.Plan(m, n), occ)
+    sup = B.Superposition(batch, np.arange(G + 1) * comps)
+    U = to_dev_c64(W.haar_unitaries(rng, G, m))
+    x = torch.randn(len(occ), dtype=torch.complex64, device=DEV)
+    gy = torch.randn(sup.out_len, dtype=torch.complex64, device=DEV)
+    a = B.fock_superposition_amplitudes_backward(sup, U, x, gy)
+    for op in (B.OP_AMPLITUDES, B.OP_AMPLITUDES_BACKWARD):
+        batch.set_config(op, B.VARIANT_FUSED)
+    b = B.fock_superposition_amplitudes_backward(sup, U, x, gy)
+    for p, q in zip(a, b):
+        assert torch.equal(p, q) is not steps
+        assert rel_err(p.cpu().numpy(), q.cpu().numpy()) <= 1e-5
+
+
+def test_groups_of_different_photon_numbers():
+    # dense inputs of 1, 2 and 3 photons on a plan for 4; with one sparse group among
+    # them every input goes component by component
+    m, rng = 6, np.random.default_rng(4)
+    say("dense inputs, mixed photon numbers")
+    for sparse in (False, True):
+        occ, off, ns = [], [0], [1, 3, 2, 3, 1]
+        for g, n in enumerate(ns):
+            basis = np.asarray(O.fock_basis(m, n), dtype=np.int32)
+            occ.append(basis[:1] if sparse and g == 1 else basis)
+            off.append(off[-1] + len(occ[-1]))
+        occ = np.concatenate(occ)
+        G = len(ns)
+        U = W.haar_unitaries(rng, G, m).astype(np.complex64)
+        x = (rng.standard_normal(len(occ)) + 1j * rng.standard_normal(len(occ))).astype(np.complex64) / np.float32(8)
+        batch = B.Batch(B.Plan(m, 4), occ)
+        sup = B.Superposition(batch, off)
+        Ud, xd = to_dev_c64(U), torch.from_numpy(x).to(DEV)
+        gy = torch.randn(sup.out_len, dtype=torch.complex64, device=DEV)
+        got = (B.fock_superposition_amplitudes(sup, Ud, xd), *B.fock_superposition_amplitudes_backward(sup, Ud, xd, gy))
+        for g, n in enumerate(ns):
+            c, o = slice(off[g], off[g + 1]), slice(sup.out_offsets[g], sup.out_offsets[g + 1])
+            amps = [O.amplitudes(widen(U[g]), s) for s in occ[c]]
+            Gg = gy[o].cpu().numpy().astype(np.complex128)
+            assert np.abs(got[0][o].cpu().numpy() - sum(complex(w) * a for w, a in zip(x[c], amps))).max() <= A_TOL
+            ref_U = sum(O.amplitude_grad(widen(U[g]), s, np.conj(complex(w)) * Gg) for w, s in zip(x[c], occ[c]))
+            assert rel_err(got[1][g].cpu().numpy(), ref_U) <= G_RTOL
+            assert rel_err(got[2][c].cpu().numpy(), np.array([np.vdot(a, Gg) for a in amps])) <= G_RTOL
+        for op in (B.OP_AMPLITUDES, B.OP_AMPLITUDES_BACKWARD):
+            batch.set_config(op, B.VARIANT_FUSED)
+        assert torch.equal(got[0], B.fock_superposition_amplitudes(sup, Ud, xd)) is sparse
