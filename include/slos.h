@@ -217,8 +217,15 @@ SLOS_API int64_t slos_batch_out_len(slos_batch_t batch);
 SLOS_API int slos_batch_out_offsets(slos_batch_t batch, int64_t* off_host);
 
 /* Device workspace needed by `op` on this batch with its current
- * configuration (0 is possible).  *bytes receives the size. */
+ * configuration (0 is possible; another configuration may need another size).
+ * *bytes receives the size; for the expectation ops the larger of the two
+ * detector models'. */
 SLOS_API int slos_workspace_bytes(slos_batch_t batch, int op, size_t* bytes);
+
+/* The same for an expectation op (SLOS_OP_MODE_EXPECTATIONS or its backward)
+ * with one detector model: 0 where photon numbers are evaluated in closed
+ * form.  SLOS_EINVAL for other ops and unknown models. */
+SLOS_API int slos_expectations_workspace_bytes(slos_batch_t batch, int op, int detector, size_t* bytes);
 
 /* Chooses the kernel variant and workgroup size used for `op` on this batch
  * (the autotuner's hook).  block = 0 keeps the library's choice; otherwise
@@ -279,7 +286,7 @@ SLOS_API int fock_probs_backward(slos_batch_t batch, const float* U, const float
  * form for any U (minors of the Gram matrix of U's input columns, FP64),
  * whatever configuration is reported.  Otherwise the fused variant
  * accumulates inside the last photon layer and never writes p; the layered
- * one writes p into the workspace first.  ws:
+ * one writes p into the workspace first.  ws: none in closed form, else
  * slos_workspace_bytes(batch, SLOS_OP_MODE_EXPECTATIONS) bytes (the layered
  * variant needs out_len * 4 bytes more than fock_probs).
  * Works on restricted plans (SLOS_PLAN_UNBUNCHED, SLOS_PLAN_DUAL_RAIL). */
@@ -288,8 +295,8 @@ SLOS_API int fock_mode_expectations(slos_batch_t batch, const float* U, float* o
 
 /* grad_U (device, complex, [B][m][m]) <- dL/dU given grad_out = dL/d<n_j>
  * (device, float, [B][m]): in closed form where the forward is (the same
- * conditions on its own op), else it forms dL/dp_t = sum_j t_j grad_out[b][j] in
- * the workspace (out_len floats) and runs the probability adjoint with the
+ * conditions on its own op; no workspace), else it forms
+ * dL/dp_t = sum_j t_j grad_out[b][j] in the workspace (out_len floats) and runs the probability adjoint with the
  * configuration set for SLOS_OP_MODE_EXPECTATIONS_BACKWARD.  Plans with
  * successor tables only (SLOS_EUNSUPPORTED otherwise). */
 SLOS_API int fock_mode_expectations_backward(slos_batch_t batch, const float* U, const float* grad_out,
@@ -320,7 +327,8 @@ SLOS_API int fock_mode_expectations_backward_ex(slos_batch_t batch, const float*
  * SLOS_OP_AMPLITUDES_BACKWARD (adjoint).  Cost: one SLOS per component, or,
  * when every group holds enough distinct components (the full Fock space, no
  * kernel variant set for the op), one pass of the whole superposition through
- * U photon by photon, sum_k N_k N_{n-k} m products per group.
+ * U photon by photon, sum_k N_k N_{n-k} m products per group, in the directions
+ * where that is sooner done.
  */
 typedef struct slos_superposition_s* slos_superposition_t;
 
@@ -332,7 +340,8 @@ SLOS_API int slos_superposition_create(slos_batch_t components, int G, const int
 SLOS_API int slos_superposition_destroy(slos_superposition_t sup);
 SLOS_API int64_t slos_superposition_out_len(slos_superposition_t sup);
 SLOS_API int slos_superposition_out_offsets(slos_superposition_t sup, int64_t* off_host);
-/* Device workspace of the forward (backward = 0) or the adjoint (1). */
+/* Device workspace of the forward (backward = 0) or the adjoint (1) with the
+ * components' current configuration; 0 where the inputs go photon by photon. */
 SLOS_API int slos_superposition_workspace_bytes(slos_superposition_t sup, int backward, size_t* bytes);
 
 /* out (device, complex, [out_len]) <- sum_c x_c a(U_g, s_c) for every group g.
@@ -408,8 +417,8 @@ SLOS_API int fock_threshold_probs(slos_batch_t batch, const float* U, float* out
 
 /* grad_U <- dL/dU given grad_out = dL/dP (device, float, [threshold_len]):
  * the probability adjoint with dL/dp_t = dL/dP(pattern of t), read through the
- * states' patterns by the fused variant of the full space and formed in the
- * workspace otherwise.  Plans with successor tables only. */
+ * states' patterns by the fused variant of the full space (no workspace) and
+ * formed in the workspace otherwise.  Plans with successor tables only. */
 SLOS_API int fock_threshold_probs_backward(slos_batch_t batch, const float* U, const float* grad_out,
                                            float* grad_U, void* ws, size_t ws_bytes, void* stream);
 
@@ -422,8 +431,8 @@ SLOS_API int fock_threshold_probs_backward(slos_batch_t batch, const float* U, c
  * state if none does.  p comes from the configuration set for
  * SLOS_OP_SAMPLE; its cumulative sums are formed in FP64 in a fixed order, so
  * equal uniforms give equal shots (on chip for samples of up to 131072
- * states, else in the workspace; slos_workspace_bytes(batch, SLOS_OP_SAMPLE)
- * bytes either way).  S >= 0. */
+ * states, else in the workspace beside p; ws:
+ * slos_workspace_bytes(batch, SLOS_OP_SAMPLE) bytes).  S >= 0. */
 SLOS_API int fock_sample(slos_batch_t batch, const float* U, const float* u, int S, int32_t* shots,
                          void* ws, size_t ws_bytes, void* stream);
 

@@ -70,6 +70,7 @@ SIGNATURES = {
     "slos_batch_out_len": (_c.c_int64, [_vp]),
     "slos_batch_out_offsets": (_c.c_int, [_vp, _vp]),
     "slos_workspace_bytes": (_c.c_int, [_vp, _c.c_int, _c.POINTER(_c.c_size_t)]),
+    "slos_expectations_workspace_bytes": (_c.c_int, [_vp, _c.c_int, _c.c_int, _c.POINTER(_c.c_size_t)]),
     "slos_batch_set_config": (_c.c_int, [_vp, _c.c_int, _c.c_int, _c.c_int]),
     "slos_batch_get_config": (_c.c_int, [_vp, _c.c_int, _c.POINTER(_c.c_int), _c.POINTER(_c.c_int)]),
     "slos_batch_set_config_ex": (_c.c_int, [_vp, _c.c_int, _c.c_int, _c.c_int, _c.c_int]),
@@ -330,8 +331,13 @@ class Batch:
     def handle(self):
         return self._h
 
-    def workspace_bytes(self, op: int) -> int:
+    def workspace_bytes(self, op: int, detector: Optional[int] = None) -> int:
+        """Bytes `op` needs; with a detector model, what an expectation op needs for that one."""
         n = ctypes.c_size_t(0)
+        if detector is not None:
+            _check("slos_expectations_workspace_bytes",
+                   lib().slos_expectations_workspace_bytes(self._h, op, detector, ctypes.byref(n)))
+            return int(n.value)
         _check("slos_workspace_bytes", lib().slos_workspace_bytes(self._h, op, ctypes.byref(n)))
         return int(n.value)
 
@@ -350,11 +356,11 @@ class Batch:
                                                                           ctypes.byref(b), ctypes.byref(t)))
         return int(v.value), int(b.value), int(t.value)
 
-    def workspace(self, op: int, device) -> Optional[torch.Tensor]:
+    def workspace(self, op: int, device, detector: Optional[int] = None) -> Optional[torch.Tensor]:
         """Device workspace for `op` on the current stream, kept by the batch
         (see WorkspaceCache: buffers are retired, never freed, so a captured
         graph's workspace outlives later calls that need more)."""
-        need = self.workspace_bytes(op)
+        need = self.workspace_bytes(op, detector)
         if need == 0:
             return None
         return self._ws.get((op, _stream_key(device)), need, device)
@@ -456,7 +462,7 @@ def fock_mode_expectations(batch: Batch, U: torch.Tensor, out: Optional[torch.Te
         out = torch.empty((batch.B, batch.m), dtype=torch.float32, device=U.device)
     _require(out, "out", torch.float32, (batch.B, batch.m))
     if ws is None:
-        ws = batch.workspace(OP_MODE_EXPECTATIONS, U.device)
+        ws = batch.workspace(OP_MODE_EXPECTATIONS, U.device, _detector(detector))
     wp, wn = _ws_args(ws)
     _check("fock_mode_expectations_ex",
            lib().fock_mode_expectations_ex(batch.handle, _ptr(U), _ptr(out), _detector(detector), wp, wn,
@@ -473,7 +479,7 @@ def fock_mode_expectations_backward(batch: Batch, U: torch.Tensor, grad_out: tor
         out = torch.empty_like(U)
     _require(out, "grad_U", torch.complex64, (batch.B, batch.m, batch.m))
     if ws is None:
-        ws = batch.workspace(OP_MODE_EXPECTATIONS_BACKWARD, U.device)
+        ws = batch.workspace(OP_MODE_EXPECTATIONS_BACKWARD, U.device, _detector(detector))
     wp, wn = _ws_args(ws)
     _check("fock_mode_expectations_backward_ex",
            lib().fock_mode_expectations_backward_ex(batch.handle, _ptr(U), _ptr(grad_out), _ptr(out),

@@ -759,8 +759,10 @@ bool variant_fused(int v) { return v == SLOS_VARIANT_FUSED || v == SLOS_VARIANT_
 
 // the expectation ops keep dL/dp or p (out_len floats) at the start of their workspace
 size_t expect_head_bytes(const slos_batch_s& Bt) { return align256((size_t)Bt.off_host[Bt.B] * sizeof(float)); }
-// sampling keeps p, the FP64 cumulative sums and the chunk totals
+// sampling keeps p and, where they do not fit on chip, the FP64 cumulative sums
+// and the chunk totals
 size_t sample_head_bytes(const slos_batch_s& Bt) {
+    if (sample_direct_ok(Bt)) return expect_head_bytes(Bt);
     return expect_head_bytes(Bt) + align256((size_t)Bt.off_host[Bt.B] * sizeof(double)) +
            align256((size_t)Bt.B * mode_expect_chunks(Bt) * sizeof(double));
 }
@@ -830,7 +832,26 @@ int resolve(const slos_batch_s& Bt, int op, int* variant, int* block) {
     return SLOS_OK;
 }
 
+// Whether an expectation op is evaluated in closed form: photon numbers of the
+// full space need no Fock space (a variant set for the op takes the recursion).
+bool expect_closed(const slos_batch_s& Bt, int op, bool clicks) {
+    return !clicks && Bt.cfg[op].variant == SLOS_VARIANT_AUTO && Bt.cfg[op].block == 0 && expect_closed_ok(Bt);
+}
+
+// Whether the click-pattern adjoint of this variant reads dL/dP itself.
+bool clicks_in_place(const slos_batch_s& Bt, int v) { return variant_fused(v) && !restricted_plan(*Bt.plan); }
+
 }  // namespace
+
+extern "C" int slos_expectations_workspace_bytes(slos_batch_t batch, int op, int detector, size_t* bytes) {
+    if (!batch || !bytes) return fail(SLOS_EINVAL, "slos_expectations_workspace_bytes: NULL argument");
+    if (!op_valid(op) || !op_expect(op)) return fail(SLOS_EINVAL, "slos_expectations_workspace_bytes: bad op");
+    if (detector != SLOS_DETECTOR_PNR && detector != SLOS_DETECTOR_THRESHOLD)
+        return fail(SLOS_EINVAL, "slos_expectations_workspace_bytes: unknown detector model");
+    if (!expect_closed(*batch, op, detector == SLOS_DETECTOR_THRESHOLD)) return slos_workspace_bytes(batch, op, bytes);
+    *bytes = 0;
+    return SLOS_OK;
+}
 
 extern "C" int slos_workspace_bytes(slos_batch_t batch, int op, size_t* bytes) {
     if (!batch || !bytes) return fail(SLOS_EINVAL, "slos_workspace_bytes: NULL argument");
@@ -846,7 +867,8 @@ extern "C" int slos_workspace_bytes(slos_batch_t batch, int op, size_t* bytes) {
     if (op == SLOS_OP_MODE_EXPECTATIONS && v != SLOS_VARIANT_FUSED)
         *bytes += expect_head_bytes(*batch) + align256(mode_expect_part_bytes(*batch));
     // the threshold ops keep p or dL/dp in the workspace
-    if (op_threshold(op)) *bytes += expect_head_bytes(*batch);
+    if (op == SLOS_OP_THRESHOLD_PROBS || (op == SLOS_OP_THRESHOLD_PROBS_BACKWARD && !clicks_in_place(*batch, v)))
+        *bytes += expect_head_bytes(*batch);
     if (op == SLOS_OP_SAMPLE) *bytes += sample_head_bytes(*batch);
     return SLOS_OK;
 }
@@ -912,18 +934,16 @@ int run_expect(const slos_batch_s& Bt, int op, int v, int blk, const float* U, c
                void* ws, size_t ws_bytes, hipStream_t s, const std::string& nm, bool clicks) {
     const bool bwd = op == SLOS_OP_MODE_EXPECTATIONS_BACKWARD;
     const bool fused = v == SLOS_VARIANT_FUSED;
-    // photon numbers of the full space need no Fock space (a variant set for the op takes the recursion)
-    const bool closed = !clicks && Bt.cfg[op].variant == SLOS_VARIANT_AUTO && Bt.cfg[op].block == 0 && expect_closed_ok(Bt);
-    if (!bwd && fused && !closed) return launch_fused_fwd(Bt, blk, (const float2*)U, out, clicks ? 3 : 2, s);
+    if (expect_closed(Bt, op, clicks))
+        return launch_expect_closed(Bt, bwd, (const float2*)U, (const float*)gin, bwd ? nullptr : (float*)out,
+                                    bwd ? (float2*)out : nullptr, s);
+    if (!bwd && fused) return launch_fused_fwd(Bt, blk, (const float2*)U, out, clicks ? 3 : 2, s);
     // workspace: [p or dL/dp][partial sums (forward)][layered workspace]
     const size_t head = expect_head_bytes(Bt);
     const size_t parts = bwd ? 0 : align256(mode_expect_part_bytes(Bt));
-    const size_t need = !bwd && fused ? 0 : head + parts + (fused ? 0 : layered_ws_bytes(Bt, bwd));
-    if (need > 0 && (!ws || ws_bytes < need))
+    const size_t need = head + parts + (fused ? 0 : layered_ws_bytes(Bt, bwd));
+    if (!ws || ws_bytes < need)
         return fail(SLOS_EWORKSPACE, nm + ": workspace missing or too small (need " + std::to_string(need) + " bytes)");
-    if (closed)
-        return launch_expect_closed(Bt, bwd, (const float2*)U, (const float*)gin, bwd ? nullptr : (float*)out,
-                                    bwd ? (float2*)out : nullptr, s);
     float* pv = (float*)ws;
     void* rest = (char*)ws + head + parts;
     int rc;
@@ -949,6 +969,7 @@ int run_threshold(const slos_batch_s& Bt, int op, int v, int blk, const float* U
         return fail(SLOS_EUNSUPPORTED, nm + ": plan was created without SLOS_PLAN_THRESHOLD");
     const bool bwd = op == SLOS_OP_THRESHOLD_PROBS_BACKWARD;
     const bool fused = variant_fused(v);
+    if (bwd && clicks_in_place(Bt, v)) return launch_fused_bwd(Bt, blk, (const float2*)U, gin, 2, (float2*)out, s);
     const size_t head = expect_head_bytes(Bt);
     const size_t need = head + (fused ? 0 : layered_ws_bytes(Bt, bwd));
     if (!ws || ws_bytes < need)
@@ -966,8 +987,6 @@ int run_threshold(const slos_batch_s& Bt, int op, int v, int blk, const float* U
         if (rc == SLOS_OK) rc = launch_threshold_gather(Bt, pv, (float*)out, s);
         return rc;
     }
-    if (fused && (Bt.plan->flags & (SLOS_PLAN_UNBUNCHED | SLOS_PLAN_DUAL_RAIL)) == 0)
-        return launch_fused_bwd(Bt, blk, (const float2*)U, gin, 2, (float2*)out, s);
     rc = launch_threshold_scatter(Bt, (const float*)gin, pv, s);
     if (rc != SLOS_OK) return rc;
     return fused ? launch_fused_bwd(Bt, blk, (const float2*)U, pv, 1, (float2*)out, s)
@@ -1050,8 +1069,18 @@ struct slos_superposition_s {
 
 namespace {
 
+// Dense inputs go photon by photon unless a kernel variant was set for the
+// components' op (which runs one simulation per component).
+bool dense_steps(const slos_superposition_s& S, int op) {
+    const Config& c = S.batch->cfg[op];
+    return (op_backward(op) ? S.dev.dense_bwd : S.dev.dense_fwd) && c.variant == SLOS_VARIANT_AUTO && c.block == 0;
+}
+
+// Bytes of the workspace's parts; none for dense inputs, which stay on chip.
 size_t sup_ws_parts(const slos_superposition_s& S, bool bwd, size_t* uc, size_t* a, size_t* ga, size_t* guc,
                     size_t* amp) {
+    *uc = *a = *ga = *guc = *amp = 0;
+    if (dense_steps(S, bwd ? SLOS_OP_AMPLITUDES_BACKWARD : SLOS_OP_AMPLITUDES)) return 0;
     const slos_batch_s& Bt = *S.batch;
     const size_t mm = (size_t)Bt.plan->m * Bt.plan->m;
     *uc = align256((size_t)Bt.B * mm * 8);
@@ -1066,13 +1095,6 @@ size_t sup_ws_parts(const slos_superposition_s& S, bool bwd, size_t* uc, size_t*
         *amp = std::max(*amp, w);
     }
     return *uc + *a + *ga + *guc + align256(*amp);
-}
-
-// Dense inputs go photon by photon unless a kernel variant was set for the
-// components' op (which runs one simulation per component).
-bool dense_steps(const slos_superposition_s& S, int op) {
-    const Config& c = S.batch->cfg[op];
-    return (op_backward(op) ? S.dev.dense_bwd : S.dev.dense_fwd) && c.variant == SLOS_VARIANT_AUTO && c.block == 0;
 }
 
 }  // namespace
@@ -1220,7 +1242,7 @@ extern "C" int fock_superposition_amplitudes(slos_superposition_t sup, const flo
     if (!U || !x || !out) return fail(SLOS_EINVAL, nm + ": NULL device pointer");
     size_t uc, a, ga, guc, amp;
     const size_t need = sup_ws_parts(*sup, false, &uc, &a, &ga, &guc, &amp);
-    if (!ws || ws_bytes < need)
+    if (need > 0 && (!ws || ws_bytes < need))
         return fail(SLOS_EWORKSPACE, nm + ": workspace missing or too small (need " + std::to_string(need) + " bytes)");
     char* base = (char*)ws;
     float2* Uc = (float2*)base;
@@ -1246,7 +1268,7 @@ extern "C" int fock_superposition_amplitudes_backward(slos_superposition_t sup, 
     if (!U || !x || !grad_out || !grad_U) return fail(SLOS_EINVAL, nm + ": NULL device pointer");
     size_t uc, a, ga, guc, amp;
     const size_t need = sup_ws_parts(*sup, true, &uc, &a, &ga, &guc, &amp);
-    if (!ws || ws_bytes < need)
+    if (need > 0 && (!ws || ws_bytes < need))
         return fail(SLOS_EWORKSPACE, nm + ": workspace missing or too small (need " + std::to_string(need) + " bytes)");
     char* base = (char*)ws;
     float2* Uc = (float2*)base;

@@ -246,6 +246,8 @@ int launch_abs2(int64_t n, const float2* a, float* p, hipStream_t stream);
 int launch_abs2_backward(int64_t n, const float2* a, const float* gp, float2* ga, hipStream_t stream);
 // z[0..n) = 0 by a fill kernel (capture-safe, unlike a memset node)
 int launch_zero_c64(int64_t n, float2* z, hipStream_t stream);
+// whether the cumulative sums of every sample are kept on chip (part and cdf unused)
+bool sample_direct_ok(const slos_batch_s& Bt);
 int launch_sample(const slos_batch_s& Bt, const float* p, double* part, double* cdf, const float* u, int S,
                   int32_t* shots, hipStream_t stream);
 

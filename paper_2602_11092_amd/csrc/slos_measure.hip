@@ -510,17 +510,18 @@ int launch_threshold_scatter(const slos_batch_s& Bt, const float* gP, float* gp,
     return launch_threshold((const void*)&threshold_scatter_kernel, (int)mode_expect_chunks(Bt), Bt, gP, gp, stream, "threshold scatter");
 }
 
+bool sample_direct_ok(const slos_batch_s& Bt) { return Bt.plan->N[Bt.n_max] <= kDirectStates; }
+
 int launch_sample(const slos_batch_s& Bt, const float* p, double* part, double* cdf, const float* u, int S,
                   int32_t* shots, hipStream_t stream) {
-    const int64_t Nmax = Bt.plan->N[Bt.n_max];
-    if (Nmax <= kDirectStates) {
+    if (sample_direct_ok(Bt)) {
         if (S == 0) return SLOS_OK;
         const int block = direct_block(Bt);
         // a workgroup per sample, more where samples alone leave CUs idle (each
         // then sums its sample again), never with fewer shots than threads
         const int64_t fill = std::max<int64_t>(1, 2 * (int64_t)std::max(Bt.plan->num_cu, 1) / Bt.B);
         int parts = (int)std::min<int64_t>(fill, ((int64_t)S + block - 1) / block);
-        const size_t lds = (size_t)((Nmax + kRun - 1) / kRun) * sizeof(double);
+        const size_t lds = (size_t)((Bt.plan->N[Bt.n_max] + kRun - 1) / kRun) * sizeof(double);
         void* fn = block == 256 ? (void*)&sample_direct_kernel<256> : (void*)&sample_direct_kernel<1024>;
         (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         // a dimension of a launch holds less than 2^32 threads
