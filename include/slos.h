@@ -243,6 +243,11 @@ SLOS_API int slos_batch_get_config(slos_batch_t batch, int op, int* variant, int
  * takes per iteration in the two-sample forward (2, 4 or 8; 0 = default 4).
  * Other variants take tile = 0 only (SLOS_EINVAL otherwise). */
 SLOS_API int slos_batch_set_config_ex(slos_batch_t batch, int op, int variant, int block, int tile);
+/* The route that `like`, a batch of the same plan, takes for `op` now, whatever
+ * the automatic choice would be for `batch`'s own size: what a test of a few
+ * samples needs to run the kernels of a large batch.  SLOS_EUNSUPPORTED if
+ * this batch cannot take that route, SLOS_EINVAL for another plan. */
+SLOS_API int slos_batch_set_config_like(slos_batch_t batch, int op, slos_batch_t like);
 /* Reads back (variant, block, tile); tile is 0 for variants without one. */
 SLOS_API int slos_batch_get_config_ex(slos_batch_t batch, int op, int* variant, int* block, int* tile);
 

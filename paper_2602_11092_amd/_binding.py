@@ -74,6 +74,7 @@ SIGNATURES = {
     "slos_batch_set_config": (_c.c_int, [_vp, _c.c_int, _c.c_int, _c.c_int]),
     "slos_batch_get_config": (_c.c_int, [_vp, _c.c_int, _c.POINTER(_c.c_int), _c.POINTER(_c.c_int)]),
     "slos_batch_set_config_ex": (_c.c_int, [_vp, _c.c_int, _c.c_int, _c.c_int, _c.c_int]),
+    "slos_batch_set_config_like": (_c.c_int, [_vp, _c.c_int, _vp]),
     "slos_batch_get_config_ex": (_c.c_int, [_vp, _c.c_int, _c.POINTER(_c.c_int), _c.POINTER(_c.c_int),
                                             _c.POINTER(_c.c_int)]),
     "fock_amplitudes": (_c.c_int, [_vp, _vp, _vp, _vp, _c.c_size_t, _vp]),
@@ -343,6 +344,10 @@ class Batch:
 
     def set_config(self, op: int, variant: int, block: int = 0, tile: int = 0):
         _check("slos_batch_set_config_ex", lib().slos_batch_set_config_ex(self._h, op, variant, block, tile))
+
+    def set_config_like(self, op: int, like: "Batch"):
+        """The route `like` (a batch of the same plan) takes for `op`, whatever this batch's size."""
+        _check("slos_batch_set_config_like", lib().slos_batch_set_config_like(self._h, op, like.handle))
 
     def get_config(self, op: int) -> Tuple[int, int]:
         v, b = ctypes.c_int(0), ctypes.c_int(0)

@@ -121,6 +121,7 @@ class _Gate:
             rows = batch.occ[batch.n == n]
             occ += [rows[0], rows[-1]]
         self.batch = B.Batch(batch.plan, np.asarray(occ, dtype=np.int32))
+        self.tuned = batch
         m, G = batch.m, len(occ)
         z = (rng.standard_normal((G, m, m)) + 1j * rng.standard_normal((G, m, m))) / np.sqrt(2.0)
         q, r = np.linalg.qr(z)
@@ -151,7 +152,10 @@ class _Gate:
         return self.inputs[op]
 
     def _run(self, op: int, cfg) -> np.ndarray:
-        self.batch.set_config(op, *cfg)
+        if cfg == AUTO:  # the kernels the tuned batch would run, not those of two samples
+            self.batch.set_config_like(op, self.tuned)
+        else:
+            self.batch.set_config(op, *cfg)
         fn, out = _runner(self.batch, self.U, op, self._input(op))
         fn()
         torch.cuda.synchronize()

@@ -364,7 +364,13 @@ int halves_ntiles(const HalvesDev& H) {
 
 }  // namespace
 
-// Every sample the same photon number, a space large enough that layers miss the
+// Every sample the same photon number, in a space whose tables the plan holds.
+bool halves_served(const slos_batch_s& Bt) {
+    if (Bt.B < 1 || Bt.n_min != Bt.n_max || Bt.n_max > kHalvesMaxN) return false;
+    return Bt.plan->halves[Bt.n_max].n != 0 && Bt.plan->N[Bt.n_max] <= kHalvesMaxStates;
+}
+
+// A space large enough that layers miss the
 // caches, and outputs enough to pay for the n + 2 launches and their tables.
 // Both sides measured, us, layer by layer against two halves.  n = 8: m = 22 (4.3
 // million states) 4 samples 167 / 166, m = 23 (5.9) 1 sample 104 / 91, m = 24
@@ -375,11 +381,9 @@ int halves_ntiles(const HalvesDev& H) {
 // samples 207 / 159.  n = 5 gains 10 % at most (m = 32, 32 samples 81 / 73) and is
 // left to the layers.
 bool halves_ok(const slos_batch_s& Bt) {
-    if (Bt.B < 1 || Bt.n_min != Bt.n_max || Bt.n_max > kHalvesMaxN) return false;
-    const HalvesDev& H = Bt.plan->halves[Bt.n_max];
+    if (!halves_served(Bt)) return false;
     const int64_t N = Bt.plan->N[Bt.n_max];
-    if (H.n == 0 || N > kHalvesMaxStates) return false;
-    return N >= 5000000 || N * Bt.B >= (H.n == 6 ? 8000000 : 16000000);
+    return N >= 5000000 || N * Bt.B >= (Bt.n_max == 6 ? 8000000 : 16000000);
 }
 
 // Samples per pass: equal passes whose factor tables stay below kHalvesWsBytes.

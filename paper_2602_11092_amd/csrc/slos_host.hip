@@ -805,6 +805,7 @@ int pairs_tile(const slos_batch_s& Bt, int op) {
 bool auto_halves(const slos_batch_s& Bt, int op) {
     if (op != SLOS_OP_AMPLITUDES && op != SLOS_OP_PROBS) return false;
     const Config& c = Bt.cfg[op];
+    if (c.halves) return true;
     if (c.variant != SLOS_VARIANT_AUTO || c.block != 0 || !halves_ok(Bt)) return false;
     return !fused_fwd_supported(*Bt.plan, Bt.n_max, fused_block_for(Bt, op), nullptr);
 }
@@ -904,10 +905,33 @@ extern "C" int slos_batch_set_config_ex(slos_batch_t batch, int op, int variant,
     }
     if (tile != 0 && !(variant == SLOS_VARIANT_FUSED_PAIRS && (tile == 2 || tile == 4 || tile == 8)))
         return fail(SLOS_EINVAL, "slos_batch_set_config_ex: tile must be 0, or 2, 4 or 8 with the two-sample variant");
+    batch->cfg[op] = Config{};
     batch->cfg[op].variant = variant;
     batch->cfg[op].block = block;
     batch->cfg[op].tile = tile;
     return SLOS_OK;
+}
+
+extern "C" int slos_batch_set_config_like(slos_batch_t batch, int op, slos_batch_t like) {
+    if (!batch || !like) return fail(SLOS_EINVAL, "slos_batch_set_config_like: NULL argument");
+    if (!op_valid(op)) return fail(SLOS_EINVAL, "slos_batch_set_config_like: bad op");
+    if (batch->plan != like->plan) return fail(SLOS_EINVAL, "slos_batch_set_config_like: batches of different plans");
+    if (auto_halves(*like, op)) {
+        if (!halves_served(*batch))
+            return fail(SLOS_EUNSUPPORTED, "slos_batch_set_config_like: this batch cannot take the two halves");
+        batch->cfg[op] = Config{};
+        batch->cfg[op].halves = true;
+        return SLOS_OK;
+    }
+    if (op_expect(op) && expect_closed(*like, op, false)) {
+        if (!expect_closed_ok(*batch))
+            return fail(SLOS_EUNSUPPORTED, "slos_batch_set_config_like: this batch cannot take the closed form");
+        batch->cfg[op] = Config{};
+        return SLOS_OK;
+    }
+    int v, blk;
+    resolve(*like, op, &v, &blk);
+    return slos_batch_set_config_ex(batch, op, v, blk, v == SLOS_VARIANT_FUSED_PAIRS ? pairs_tile(*like, op) : 0);
 }
 
 extern "C" int slos_batch_get_config(slos_batch_t batch, int op, int* variant, int* block) {

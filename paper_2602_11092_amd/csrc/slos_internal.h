@@ -107,6 +107,7 @@ struct HalvesDev {
 struct Config {
     int variant = SLOS_VARIANT_AUTO;
     int block = 0;
+    bool halves = false;  // AUTO: the two halves whatever the size rules say (slos_batch_set_config_like)
     int tile = 0;  // states per thread of the variant's main loop (0: its default)
 };
 
@@ -182,7 +183,8 @@ int launch_layered_bwd(const slos_batch_s& Bt, int block, const float2* U, const
                        float2* gU, void* ws, hipStream_t stream);
 
 // ---- two halves (workspace-resident, any size): slos_halves.hip ----
-// whether a batch (every sample the same photon number) can take it
+// whether a batch (every sample the same photon number) can take it, and whether it should
+bool halves_served(const slos_batch_s& Bt);
 bool halves_ok(const slos_batch_s& Bt);
 size_t halves_ws_bytes(const slos_batch_s& Bt);
 int launch_halves_fwd(const slos_batch_s& Bt, const float2* U, void* out, bool probs, void* ws, hipStream_t stream);

@@ -114,3 +114,25 @@ def test_autotune_cache_round_trip(tmp_path):
     json.dump(data, open(path, "w"))
     rep3 = autotune(B.Batch(batch.plan, occ), Ud, ops=(B.OP_PROBS,), warmup=1, iters=1, cache=path)
     assert not rep3[B.OP_PROBS]["cached"] and rep3[B.OP_PROBS]["timings"]
+
+
+# uniform batches that the automatic choice sends through the two halves, through
+# the two-sample kernel, and per-mode expectations in closed form; the gate's own
+# two samples are too few for the first two
+@pytest.mark.parametrize("op,m,n,Bn", [(B.OP_PROBS, 28, 6, 8), (B.OP_AMPLITUDES, 26, 7, 5), (B.OP_PROBS, 12, 5, 300),
+                                       (B.OP_MODE_EXPECTATIONS, 8, 4, 5), (B.OP_PROBS, 8, 3, 40)])
+def test_gate_runs_the_route_of_the_tuned_batch(op, m, n, Bn):
+    from paper_2602_11092_amd.autotune import AUTO, REFERENCE, _Gate
+    say("gate", op, m, n, Bn)
+    occ = np.zeros((Bn, m), dtype=np.int32)
+    occ[:, :n] = 1
+    batch = B.Batch(B.Plan(m, n), occ)
+    assert batch.get_config(op)[0] != B.VARIANT_AUTO
+    gate = _Gate(batch, DEV)
+    assert gate.passes(op, AUTO)
+    if m >= 26 or op == B.OP_MODE_EXPECTATIONS:  # other arithmetic than the layers: other rounding
+        assert not np.array_equal(gate._run(op, AUTO), gate._run(op, REFERENCE))
+    else:
+        gate._run(op, AUTO)
+        assert gate.batch.get_config_ex(op) == batch.get_config_ex(op)
+        assert (gate.batch.get_config(op)[0] == B.VARIANT_FUSED_PAIRS) == (Bn == 300)
