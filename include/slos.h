@@ -243,6 +243,10 @@ SLOS_API int slos_batch_get_config(slos_batch_t batch, int op, int* variant, int
  * takes per iteration in the two-sample forward (2, 4 or 8; 0 = default 4).
  * Other variants take tile = 0 only (SLOS_EINVAL otherwise). */
 SLOS_API int slos_batch_set_config_ex(slos_batch_t batch, int op, int variant, int block, int tile);
+/* slos_batch_set_config_ex for a choice made by timing the op's own calls: dense
+ * amplitude-encoded inputs over this batch keep going through U photon by
+ * photon, which an explicitly set variant turns off. */
+SLOS_API int slos_batch_set_config_tuned(slos_batch_t batch, int op, int variant, int block, int tile);
 /* The route that `like`, a batch of the same plan, takes for `op` now, whatever
  * the automatic choice would be for `batch`'s own size: what a test of a few
  * samples needs to run the kernels of a large batch.  SLOS_EUNSUPPORTED if
@@ -331,7 +335,7 @@ SLOS_API int fock_mode_expectations_backward_ex(slos_batch_t batch, const float*
  * the batch's configuration for SLOS_OP_AMPLITUDES (forward) and
  * SLOS_OP_AMPLITUDES_BACKWARD (adjoint).  Cost: one SLOS per component, or,
  * when every group holds enough distinct components (the full Fock space, no
- * kernel variant set for the op), one pass of the whole superposition through
+ * kernel variant set for the op but by slos_batch_set_config_tuned), one pass of the whole superposition through
  * U photon by photon, sum_k N_k N_{n-k} m products per group, in the directions
  * where that is sooner done.
  */

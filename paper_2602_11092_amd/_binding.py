@@ -74,6 +74,7 @@ SIGNATURES = {
     "slos_batch_set_config": (_c.c_int, [_vp, _c.c_int, _c.c_int, _c.c_int]),
     "slos_batch_get_config": (_c.c_int, [_vp, _c.c_int, _c.POINTER(_c.c_int), _c.POINTER(_c.c_int)]),
     "slos_batch_set_config_ex": (_c.c_int, [_vp, _c.c_int, _c.c_int, _c.c_int, _c.c_int]),
+    "slos_batch_set_config_tuned": (_c.c_int, [_vp, _c.c_int, _c.c_int, _c.c_int, _c.c_int]),
     "slos_batch_set_config_like": (_c.c_int, [_vp, _c.c_int, _vp]),
     "slos_batch_get_config_ex": (_c.c_int, [_vp, _c.c_int, _c.POINTER(_c.c_int), _c.POINTER(_c.c_int),
                                             _c.POINTER(_c.c_int)]),
@@ -327,6 +328,7 @@ class Batch:
         self.threshold_offsets = toff
         self.threshold_len = int(toff[-1])
         self._ws = WorkspaceCache()
+        self._set = {}
 
     @property
     def handle(self):
@@ -342,8 +344,16 @@ class Batch:
         _check("slos_workspace_bytes", lib().slos_workspace_bytes(self._h, op, ctypes.byref(n)))
         return int(n.value)
 
-    def set_config(self, op: int, variant: int, block: int = 0, tile: int = 0):
-        _check("slos_batch_set_config_ex", lib().slos_batch_set_config_ex(self._h, op, variant, block, tile))
+    def set_config(self, op: int, variant: int, block: int = 0, tile: int = 0, tuned: bool = False):
+        """Kernel choice for `op`; `tuned`: found by timing its calls, so superpositions over the batch
+        keep a route of their own."""
+        fn = "slos_batch_set_config_tuned" if tuned else "slos_batch_set_config_ex"
+        _check(fn, getattr(lib(), fn)(self._h, op, variant, block, tile))
+        self._set[op] = (variant, block, tile, tuned)
+
+    def set_choice(self, op: int) -> Tuple[int, int, int, bool]:
+        """What set_config last set for `op` (get_config tells what the library makes of it)."""
+        return self._set.get(op, (VARIANT_AUTO, 0, 0, False))
 
     def set_config_like(self, op: int, like: "Batch"):
         """The route `like` (a batch of the same plan) takes for `op`, whatever this batch's size."""

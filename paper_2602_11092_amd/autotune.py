@@ -251,7 +251,7 @@ def autotune(batch: B.Batch, U: torch.Tensor, ops: Iterable[int] = (B.OP_PROBS, 
                 if hit.get("auto"):
                     batch.set_config(op, *AUTO)
                 else:
-                    batch.set_config(op, hit["variant"], hit["block"], hit.get("tile", 0))
+                    batch.set_config(op, hit["variant"], hit["block"], hit.get("tile", 0), tuned=True)
                 report[op] = {"variant": hit["variant"], "block": hit["block"], "tile": hit.get("tile", 0),
                               "us": hit["us"], "cached": True, "timings": [], "rejected": []}
                 continue
@@ -260,34 +260,40 @@ def autotune(batch: B.Batch, U: torch.Tensor, ops: Iterable[int] = (B.OP_PROBS, 
         cands = (candidates or {}).get(op) or (BACKWARD_CANDIDATES if op in _BACKWARD else FORWARD_CANDIDATES)
         if op in _AUTO_OPS and not (candidates or {}).get(op):
             cands = [AUTO, *cands]
-        before = batch.get_config_ex(op)
+        before = batch.set_choice(op)
         timings, rejected = [], []
         auto_us = None
-        for variant, block, tile in cands:
-            try:
-                batch.set_config(op, variant, block, tile)
-            except B.SlosError:
-                continue  # not supported for this batch
-            if gate is None:
-                gate = _Gate(batch, U.device)
-            if not gate.passes(op, (variant, block, tile)):
-                rejected.append((variant, block, tile))
-                continue
-            fn, _ = _runner(batch, U, op)
-            try:
-                us = _time_us(fn, warmup, iters)
-            except B.SlosError:
-                continue
-            if (variant, block, tile) == AUTO:  # listed as the configuration the library reports for it
-                variant, block, tile = batch.get_config_ex(op)
-                auto_us = us
-            timings.append((variant, block, tile, us))
-        if not timings:
+        try:
+            for variant, block, tile in cands:
+                try:
+                    batch.set_config(op, variant, block, tile)
+                except B.SlosError:
+                    continue  # not supported for this batch
+                if gate is None:
+                    gate = _Gate(batch, U.device)
+                if not gate.passes(op, (variant, block, tile)):
+                    rejected.append((variant, block, tile))
+                    continue
+                fn, _ = _runner(batch, U, op)
+                try:
+                    us = _time_us(fn, warmup, iters)
+                except B.SlosError:
+                    continue
+                if (variant, block, tile) == AUTO:  # listed as the configuration the library reports for it
+                    variant, block, tile = batch.get_config_ex(op)
+                    auto_us = us
+                timings.append((variant, block, tile, us))
+            if not timings:
+                raise RuntimeError("autotune: no configuration runs op %d on this batch" % op)
+        except BaseException:
             batch.set_config(op, *before)
-            raise RuntimeError("autotune: no configuration runs op %d on this batch" % op)
+            raise
         variant, block, tile, us = min(timings, key=lambda r: r[3])
         auto = us == auto_us
-        batch.set_config(op, *(AUTO if auto else (variant, block, tile)))
+        if auto:
+            batch.set_config(op, *AUTO)
+        else:
+            batch.set_config(op, variant, block, tile, tuned=True)
         report[op] = {"variant": variant, "block": block, "tile": tile, "us": us, "cached": False,
                       "timings": timings, "rejected": rejected}
         if cache:

@@ -912,6 +912,12 @@ extern "C" int slos_batch_set_config_ex(slos_batch_t batch, int op, int variant,
     return SLOS_OK;
 }
 
+extern "C" int slos_batch_set_config_tuned(slos_batch_t batch, int op, int variant, int block, int tile) {
+    const int rc = slos_batch_set_config_ex(batch, op, variant, block, tile);
+    if (rc == SLOS_OK) batch->cfg[op].tuned = true;
+    return rc;
+}
+
 extern "C" int slos_batch_set_config_like(slos_batch_t batch, int op, slos_batch_t like) {
     if (!batch || !like) return fail(SLOS_EINVAL, "slos_batch_set_config_like: NULL argument");
     if (!op_valid(op)) return fail(SLOS_EINVAL, "slos_batch_set_config_like: bad op");
@@ -1093,11 +1099,13 @@ struct slos_superposition_s {
 
 namespace {
 
-// Dense inputs go photon by photon unless a kernel variant was set for the
-// components' op (which runs one simulation per component).
+// Dense inputs go photon by photon unless a kernel variant was asked for by name
+// for the components' op (which runs one simulation per component); one that was
+// measured to be the op's fastest says nothing of superpositions.
 bool dense_steps(const slos_superposition_s& S, int op) {
     const Config& c = S.batch->cfg[op];
-    return (op_backward(op) ? S.dev.dense_bwd : S.dev.dense_fwd) && c.variant == SLOS_VARIANT_AUTO && c.block == 0;
+    return (op_backward(op) ? S.dev.dense_bwd : S.dev.dense_fwd) &&
+           (c.tuned || (c.variant == SLOS_VARIANT_AUTO && c.block == 0));
 }
 
 // Bytes of the workspace's parts; none for dense inputs, which stay on chip.

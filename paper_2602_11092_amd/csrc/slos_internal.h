@@ -107,6 +107,7 @@ struct HalvesDev {
 struct Config {
     int variant = SLOS_VARIANT_AUTO;
     int block = 0;
+    bool tuned = false;   // a measured choice for the op's own calls (slos_batch_set_config_tuned)
     bool halves = false;  // AUTO: the two halves whatever the size rules say (slos_batch_set_config_like)
     int tile = 0;  // states per thread of the variant's main loop (0: its default)
 };

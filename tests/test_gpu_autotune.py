@@ -136,3 +136,49 @@ def test_gate_runs_the_route_of_the_tuned_batch(op, m, n, Bn):
         gate._run(op, AUTO)
         assert gate.batch.get_config_ex(op) == batch.get_config_ex(op)
         assert (gate.batch.get_config(op)[0] == B.VARIANT_FUSED_PAIRS) == (Bn == 300)
+
+
+def test_tuning_the_components_keeps_dense_superpositions(tmp_path):
+    """Whatever the component ops are tuned to, dense inputs go through U photon
+    by photon; a variant set by name runs one simulation per component."""
+    m, n, G = 6, 3, 8
+    occ = np.tile(np.asarray(O.fock_basis(m, n), dtype=np.int32), (G, 1))
+    batch = B.Batch(B.Plan(m, n), occ)
+    sup = B.Superposition(batch, np.arange(G + 1) * (len(occ) // G))
+    rng = np.random.default_rng(2)
+    U = to_dev_c64(W.haar_unitaries(rng, G, m))
+    Uc = U.repeat_interleave(len(occ) // G, dim=0).contiguous()
+    x = torch.randn(len(occ), dtype=torch.complex64, device=DEV)
+
+    def run():
+        y = B.fock_superposition_amplitudes(sup, U, x)
+        return (y, *B.fock_superposition_amplitudes_backward(sup, U, x, torch.ones_like(y)))
+
+    want = run()
+    say("tuning the components of dense inputs")
+    ops = (B.OP_AMPLITUDES, B.OP_AMPLITUDES_BACKWARD)
+    only = {op: [(B.VARIANT_FUSED, 256, 0)] for op in ops}
+    path = str(tmp_path / "tune.json")
+    for _ in range(2):  # timed, then from the cache
+        rep = autotune(batch, Uc, ops=ops, warmup=1, iters=1, candidates=only, cache=path)
+        assert all(batch.get_config(op) == (B.VARIANT_FUSED, 256) for op in ops)
+        assert all(map(torch.equal, want, run()))
+    assert all(rep[op]["cached"] for op in ops)
+    for op in ops:
+        batch.set_config(op, B.VARIANT_FUSED, 256)
+    assert not any(map(torch.equal, want, run()))
+
+
+def test_a_failed_tuning_leaves_the_automatic_choice():
+    U64, occ = _mixed_batch(seed=3, B_=6, m=6)
+    batch = B.Batch(B.Plan(6, int(occ.sum(1).max())), occ)
+    Ud = to_dev_c64(U64)
+    op = B.OP_MODE_EXPECTATIONS
+    e = B.fock_mode_expectations(batch, Ud)
+    say("a tuning that finds nothing")
+    with pytest.raises(RuntimeError):  # 768 threads are an adjoint's size
+        autotune(batch, Ud, ops=(op,), warmup=1, iters=1, candidates={op: [(B.VARIANT_FUSED, 768, 0)]})
+    assert batch.set_choice(op)[0] == B.VARIANT_AUTO
+    assert torch.equal(e, B.fock_mode_expectations(batch, Ud))  # in closed form still
+    batch.set_config(op, B.VARIANT_FUSED, 256)
+    assert not torch.equal(e, B.fock_mode_expectations(batch, Ud))
