@@ -753,7 +753,7 @@ def mesh_workspace(m: int, B: int, device) -> torch.Tensor:
     return _mesh_ws.get(("mesh", _stream_key(device)), _mesh_bytes(m, B), device)
 
 
-@functools.lru_cache(maxsize=256)
+@functools.lru_cache(maxsize=256, typed=True)  # (20.0 is refused, also after 20)
 def _mesh_bytes(m: int, B: int) -> int:
     n = ctypes.c_size_t(0)
     _check("mesh_workspace_bytes", lib().mesh_workspace_bytes(m, B, ctypes.byref(n)))

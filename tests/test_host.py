@@ -362,3 +362,12 @@ def test_autotune_gate_comparison_and_cache_files(tmp_path):
     assert T._load_cache(path)["k1"]["1"]["tile"] == 4 and T._load_cache(path)["k1"]["3"]["block"] == 768
     open(path, "w").write("{ not json")
     assert T._load_cache(path) == {}
+
+
+def test_mesh_sizes_stay_integers():
+    # a size seen before answers from a cache, which takes 6.0 for 6 unless told not to
+    assert B._mesh_bytes(6, 5) > 0
+    with pytest.raises((TypeError, ctypes.ArgumentError)):
+        B._mesh_bytes(6.0, 5)
+    with pytest.raises((TypeError, ctypes.ArgumentError)):
+        B._mesh_bytes(6, 5.0)
