@@ -255,9 +255,7 @@ __global__ __launch_bounds__(256, 2) void halves_fwd_kernel(HalvesDev H, BatchDe
                         im[i][j] += ci[i][j];
                     }
             };
-            switch (len / 2) {
-                case 3: multiply(std::integral_constant<int, 3>{}); break;
-                case 4: multiply(std::integral_constant<int, 4>{}); break;
+            switch (len / 2) {  // inner lengths 15 to 70 in chunks of up to 16: 5 to 8 steps
                 case 5: multiply(std::integral_constant<int, 5>{}); break;
                 case 6: multiply(std::integral_constant<int, 6>{}); break;
                 case 7: multiply(std::integral_constant<int, 7>{}); break;
@@ -370,9 +368,10 @@ bool halves_served(const slos_batch_s& Bt) {
     return Bt.plan->halves[Bt.n_max].n != 0 && Bt.plan->N[Bt.n_max] <= kHalvesMaxStates;
 }
 
-// A space large enough that layers miss the
-// caches, and outputs enough to pay for the n + 2 launches and their tables.
-// Both sides measured, us, layer by layer against two halves.  n = 8: m = 22 (4.3
+// A space large enough that layers miss the caches, and outputs enough to pay for
+// the n + 2 launches and their tables: 5 million states, which is every space of 8
+// photons that has tables (the plan builds none below), or 16 (n = 7) and 8 (n = 6)
+// million outputs.  Both sides measured, us, layer by layer against two halves.  n = 8: m = 22 (4.3
 // million states) 4 samples 167 / 166, m = 23 (5.9) 1 sample 104 / 91, m = 24
 // (7.9) 1 sample 135 / 101, 16 samples 995 / 812, m = 28 (23.5) 1 sample 340 / 184.  n = 7:
 // m = 20 (0.66) 32 samples 152 / 159, m = 24 (2.0) 8 samples 118 / 121, m = 26 (3.4)
@@ -383,7 +382,7 @@ bool halves_served(const slos_batch_s& Bt) {
 bool halves_ok(const slos_batch_s& Bt) {
     if (!halves_served(Bt)) return false;
     const int64_t N = Bt.plan->N[Bt.n_max];
-    return N >= 5000000 || N * Bt.B >= (Bt.n_max == 6 ? 8000000 : 16000000);
+    return N >= 5000000 || (Bt.n_max < 8 && N * Bt.B >= (Bt.n_max == 6 ? 8000000 : 16000000));
 }
 
 // Samples per pass: equal passes whose factor tables stay below kHalvesWsBytes.

@@ -89,7 +89,7 @@ struct BatchDev {
 // Two-halves evaluation (slos_halves.h) of n-photon spaces beyond LDS: level
 // sizes and tables of the low and high mode halves.
 constexpr int kHalvesMinN = 6, kHalvesMaxN = 8;  // photon numbers with compiled instances
-// the smallest spaces for which the evaluation pays (measured at halves_ok)
+// the smallest spaces for which tables are built (the rule is halves_ok's)
 constexpr int64_t halves_min_states(int n) { return n == 6 ? 1000000 : n == 7 ? 3000000 : 5000000; }
 struct HalvesDev {
     int n = 0;                            // 0: not served

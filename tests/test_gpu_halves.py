@@ -80,3 +80,33 @@ def test_two_halves_graph_replays():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("m,n,Bn", [(28, 6, 8), (29, 6, 7), (28, 7, 2), (23, 8, 2)])
+def test_two_halves_against_64_bit_permanents(m, n, Bn):
+    """A sample of the outputs, each cut of the photons between the halves among
+    them, and the first and the last state."""
+    from oracle import oracle as O
+    U, occ = _batch(m, n, Bn, m + n)
+    batch = B.Batch(B.Plan(m, n), occ)
+    say("two halves against permanents", m, n, Bn)
+    a, p = B.fock_amplitudes(batch, U).cpu().numpy(), B.fock_probs(batch, U).cpu().numpy()
+    rng = np.random.default_rng(1)
+    ref = B.Batch(batch.plan, occ)
+    ref.set_config(B.OP_PROBS, B.VARIANT_LAYERED, 256)
+    assert not np.array_equal(p, B.fock_probs(ref, U).cpu().numpy())  # the two halves ran
+    states = []
+    for k in range(n + 1):  # k photons in the low half
+        for _ in range(20):
+            t = np.zeros(m, dtype=np.int32)
+            np.add.at(t, rng.integers(0, m // 2, size=k), 1)
+            np.add.at(t, rng.integers(m // 2, m, size=n - k), 1)
+            states.append(t)
+    for j in (0, m - 1):
+        states.append((np.arange(m) == j).astype(np.int32) * n)
+    ranks = np.array([O.fock_rank(m, n, t) for t in states])
+    for b in (0, Bn - 1):
+        want = O.amplitudes(U[b].cpu().numpy().astype(np.complex128), occ[b], outputs=np.asarray(states))
+        at = batch.offsets[b] + ranks
+        assert rel_err(a[at], want) <= REL, b
+        assert rel_err(p[at], np.abs(want) ** 2) <= 2 * REL, b
