@@ -125,3 +125,20 @@ def test_click_adjoint_workspace(unbunched):
         assert torch.equal(gU, B.fock_threshold_probs_backward(batch, U, g))
         batch.set_config(op, B.VARIANT_LAYERED)
         _refused(bare)
+
+
+def test_layers_in_a_workspace_of_any_alignment():
+    # the layers are read two complex values at a time; a workspace carved from a
+    # larger one need not begin on 16 bytes
+    batch, U = _batch(20, 5, 12)
+    say("layered workspace at 8 bytes past an allocation")
+    g = torch.randn(batch.out_len, device=DEV)
+    for op in (B.OP_PROBS, B.OP_PROBS_BACKWARD):
+        batch.set_config(op, B.VARIANT_LAYERED)
+    want = B.fock_probs(batch, U), B.fock_probs_backward(batch, U, g)
+
+    def off(op):
+        return torch.empty(batch.workspace_bytes(op) + 8, dtype=torch.uint8, device=DEV)[8:]
+
+    assert torch.equal(want[0], B.fock_probs(batch, U, ws=off(B.OP_PROBS)))
+    assert torch.equal(want[1], B.fock_probs_backward(batch, U, g, ws=off(B.OP_PROBS_BACKWARD)))
