@@ -20,8 +20,10 @@
 //   gT_k[J][I] = sum_{j <= first(J)} sum_{i in I} conj(U[j][i]) gT_{k+1}[J + e_j][I - e_i],
 //   gU[j][i]  += sum conj(T_k[J][I' + e_i]) gT_{k+1}[J + e_j][I']  over J with first(J) >= j and I'.
 //
-// T and the sums it takes are FP32; gT is carried in FP64, so that dL/dx (gT_0,
-// scaled) is rounded once.
+// The sums are FP64 and T is kept in FP32, one rounding a step; gT is carried in
+// FP64, so that dL/dx (gT_0, scaled) is rounded once.  Relative error against 64 bits,
+// m = 8, n = 3, 64 inputs, one simulation per component and here: y 2.2e-7 / 5.3e-8,
+// dL/dU 1.5e-7 / 4.1e-8, dL/dx 8.2e-8 / 2.6e-8.  (With FP32 sums dL/dU was off by 1.8e-7.)
 //
 // One workgroup per input; T, gT, U and 16-bit copies of the transition
 // tables sit in LDS (m = 6, n = 3: 9 KB).  The kernels are bound by the
@@ -41,7 +43,7 @@ struct DenseLayout {
     uint32_t T[kMaxPhotons + 1];     // T_k, float2 [N_k][N_{n-k}]
     uint32_t g[2], gn;               // gT_k at g[k & 1] for k < n, and gT_n, double2 (backward)
     uint32_t U;                      // float2 [m][m]
-    uint32_t part;                   // float2 [kDenseBlock]: partial sums of gU (backward)
+    uint32_t part;                   // double2 [kDenseBlock]: partial sums of gU (backward)
     uint32_t succ[kMaxPhotons + 1];  // uint16 [N_{l-1}][m], l = 1..n: rank of I' + e_i
     uint32_t pred[kMaxPhotons + 1];  // uint16 [N_l][l][2], l = 1..n: mode and rank of the removals, mode 0xFFFF: none
     uint32_t bytes;
@@ -64,10 +66,10 @@ __host__ __device__ inline void dense_layout(const int* N, int m, int n, bool bw
         L.g[(n - 1) & 1] = at;
         at += 2 * most[(n - 1) & 1];
     }
+    L.part = at;
+    at += bwd ? 16u * kDenseBlock : 0;
     L.U = at;
     at += 8u * (uint32_t)(m * m);
-    L.part = at;
-    at += bwd ? 8u * kDenseBlock : 0;
     for (int l = 1; l <= n; ++l) {
         L.succ[l] = at;
         at += (2u * (uint32_t)(N[l - 1] * m) + 3u) & ~3u;
@@ -95,6 +97,13 @@ struct DenseArgs {
     float2* gU;              // [G][m][m] (backward)
     float2* gx;              // [C] or nullptr (backward)
 };
+
+__device__ __forceinline__ void z_fma_conj(double2& acc, float2 a, double2 b) {  // acc += conj(a) b
+    acc.x = fma((double)a.x, b.x, acc.x);
+    acc.x = fma((double)a.y, b.y, acc.x);
+    acc.y = fma((double)a.x, b.y, acc.y);
+    acc.y = fma(-(double)a.y, b.x, acc.y);
+}
 
 // prod t! of the state whose n removals are pred (a mode's further photons are
 // marked 0xFFFF).
@@ -159,9 +168,15 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
             const int r = e / cols_n, q = e % cols_n;
             const float2* u = U + pred[2 * r * (k + 1)] * m;
             const float2* t = Tk + pred[2 * r * (k + 1) + 1] * cols_k;
-            float2 acc = c_zero();
-            for (int i = 0; i < m; ++i) c_fma(acc, u[i], t[succ[q * m + i]]);
-            Tn[e] = acc;
+            double2 acc = make_double2(0.0, 0.0);
+            for (int i = 0; i < m; ++i) {
+                const float2 a = u[i], v = t[succ[q * m + i]];
+                acc.x = fma((double)a.x, (double)v.x, acc.x);
+                acc.x = fma(-(double)a.y, (double)v.y, acc.x);
+                acc.y = fma((double)a.x, (double)v.y, acc.y);
+                acc.y = fma((double)a.y, (double)v.x, acc.y);
+            }
+            Tn[e] = make_float2((float)acc.x, (float)acc.y);
         }
         __syncthreads();
     }
@@ -182,9 +197,9 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
         // thread (i, j, part): this part's share of gU[j][i]
         const int mm = m * m;
         const int parts = max(1, kDenseBlock / mm);
-        float2 gu[(kMaxModes * kMaxModes + kDenseBlock - 1) / kDenseBlock];
+        double2 gu[(kMaxModes * kMaxModes + kDenseBlock - 1) / kDenseBlock];
 #pragma unroll
-        for (auto& v : gu) v = c_zero();
+        for (auto& v : gu) v = make_double2(0.0, 0.0);
         for (int k = n - 1; k >= 0; --k) {
             const float2* Tk = (const float2*)(dlds + L.T[k]);
             const double2* gu1 = (const double2*)(dlds + (k + 1 == n ? L.gn : L.g[(k + 1) & 1]));
@@ -205,8 +220,7 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
                 for (int r = lo; r < hi; ++r) {
                     const float2* t = Tk + predJ[2 * r * (k + 1) + 1] * cols_k;
                     for (int q = part; q < cols_n; q += parts) {
-                        const double2 v = gu1[r * cols_n + q];
-                        c_fma_conj(gu[w], t[succI[q * m + i]], make_float2((float)v.x, (float)v.y));
+                        z_fma_conj(gu[w], t[succI[q * m + i]], gu1[r * cols_n + q]);
                     }
                 }
             }
@@ -218,14 +232,7 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
                     const int i = predI[2 * (I * (n - k) + p)];
                     if (i == 0xFFFF) continue;
                     const double2* gq = gu1 + predI[2 * (I * (n - k) + p) + 1];
-                    for (int j = 0; j <= first; ++j) {  // acc += conj(U[j][i]) g
-                        const float2 u = U[j * m + i];
-                        const double2 v = gq[succJ[J * m + j] * cols_n];
-                        acc.x = fma((double)u.x, v.x, acc.x);
-                        acc.x = fma((double)u.y, v.y, acc.x);
-                        acc.y = fma((double)u.x, v.y, acc.y);
-                        acc.y = fma(-(double)u.y, v.x, acc.y);
-                    }
+                    for (int j = 0; j <= first; ++j) z_fma_conj(acc, U[j * m + i], gq[succJ[J * m + j] * cols_n]);
                 }
                 gk[e] = acc;
             }
@@ -239,20 +246,23 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
                 A.gx[c] = make_float2((float)(f * g0[s].x), (float)(f * g0[s].y));
             }
         }
-        float2* part = (float2*)(dlds + L.part);
+        double2* part = (double2*)(dlds + L.part);
         if (parts > 1) {  // one pass: parts * mm <= kDenseBlock
             part[tid] = gu[0];
             __syncthreads();
             if (tid < mm) {
-                float2 v = part[tid];
-                for (int q = 1; q < parts; ++q) v = c_add(v, part[q * mm + tid]);
-                A.gU[(size_t)g * mm + tid] = (cols >> (tid % m)) & 1 ? v : c_zero();
+                double2 v = part[tid];
+                for (int q = 1; q < parts; ++q) {
+                    v.x += part[q * mm + tid].x;
+                    v.y += part[q * mm + tid].y;
+                }
+                A.gU[(size_t)g * mm + tid] = (cols >> (tid % m)) & 1 ? make_float2((float)v.x, (float)v.y) : c_zero();
             }
         } else {
 #pragma unroll
             for (int w = 0; w < (int)(sizeof(gu) / sizeof(gu[0])); ++w) {
                 const int e = tid + w * kDenseBlock;
-                if (e < mm) A.gU[(size_t)g * mm + e] = (cols >> (e % m)) & 1 ? gu[w] : c_zero();
+                if (e < mm) A.gU[(size_t)g * mm + e] = (cols >> (e % m)) & 1 ? make_float2((float)gu[w].x, (float)gu[w].y) : c_zero();
             }
         }
     }
@@ -290,9 +300,9 @@ bool dense_superposition_ok(const slos_plan_s& P, int n, int64_t comps) {
 // and walks an input's components one after another only to combine them.  Both
 // fitted, us, to measurements at 19 spaces (1 to 256 inputs, the fewest
 // components and all of them): the adjoint's chain 4 + 4 n + (0.7 + 0.65 n) per 1000
-// products, the forward's a 3.6th; one simulation per component 12 + 1.5 n + 0.055 m^2,
+// products, the forward's a 3.6th; one simulation per component 14 + 1.5 n + 0.055 m^2,
 // 0.23 per component of an input and 0.022 or more per component beyond 512 (without
-// dL/dx, as in training with fixed inputs), the forward 11, 0.5 and 0.006.  Either side
+// dL/dx, as in training with fixed inputs), the forward 11, 0.52 and 0.006.  Either side
 // of the line, steps / components: adjoint m = 8, n = 4, 17 of 330 states, 16 inputs 115
 // / 35, 256 inputs 115 / 133, all states, 4 inputs 115 / 142; m = 6, n = 4, 11 of 126, 1
 // input 45 / 30, all 45 / 59; m = 3, n = 8, all 45, 16 inputs 57 / 56, 64 inputs 56 / 133;
@@ -309,9 +319,9 @@ bool dense_superposition_sooner(const slos_plan_s& P, int n, int64_t comps, int6
     const int64_t at_once = std::max(P.num_cu, 1) * (int64_t)(160 * 1024 / dense_lds(P, n, bwd));
     const double rounds = (double)((inputs + at_once - 1) / at_once);
     const double chain = (4.0 + 4.0 * n + steps * (0.7 + 0.65 * n) * 1e-3) * rounds;
-    if (!bwd) return chain / 3.6 <= 11.0 + 0.5 * comps + 0.006 * beyond;
+    if (!bwd) return chain / 3.6 <= 11.0 + 0.52 * comps + 0.006 * beyond;
     const double each = std::max(0.022, std::max(0.012e-3 * single, 0.9e-4 * mm));
-    return chain <= 12.0 + 1.5 * n + 0.055 * mm + 0.23 * comps + each * beyond;
+    return chain <= 14.0 + 1.5 * n + 0.055 * mm + 0.23 * comps + each * beyond;
 }
 
 int launch_dense_superposition(const SupDev& S, const slos_batch_s& Bt, bool bwd, const float2* U, const float2* x,

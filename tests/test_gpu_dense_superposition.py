@@ -173,3 +173,37 @@ def test_groups_of_different_photon_numbers():
         for op in (B.OP_AMPLITUDES, B.OP_AMPLITUDES_BACKWARD):
             batch.set_config(op, B.VARIANT_FUSED)
         assert torch.equal(got[0], B.fock_superposition_amplitudes(sup, Ud, xd)) is sparse
+
+
+@pytest.mark.parametrize("m,n", [(2, 2), (6, 3), (8, 3), (5, 4), (12, 2), (6, 4)])
+def test_steps_are_no_further_off_than_components(m, n):
+    # every output against 64 bits, by the steps and by one simulation per component
+    rng = np.random.default_rng(100 * m + n)
+    G = 4
+    basis = np.asarray(O.fock_basis(m, n), dtype=np.int32)
+    N = len(basis)
+    say("errors of dense inputs", m, n)
+    U = W.haar_unitaries(rng, G, m).astype(np.complex64)
+    x, gy = ((rng.standard_normal((G, N)) + 1j * rng.standard_normal((G, N))).astype(np.complex64) for _ in range(2))
+    batch = B.Batch(B.Plan(m, n), np.tile(basis, (G, 1)))
+    sup = B.Superposition(batch, np.arange(G + 1) * N)
+    Ud, xd, gd = to_dev_c64(U), torch.from_numpy(x.ravel()).to(DEV), torch.from_numpy(gy.ravel()).to(DEV)
+
+    def run():
+        out = (B.fock_superposition_amplitudes(sup, Ud, xd), *B.fock_superposition_amplitudes_backward(sup, Ud, xd, gd))
+        return [v.cpu().numpy().reshape(G, -1) for v in out]
+
+    steps = run()
+    for op in (B.OP_AMPLITUDES, B.OP_AMPLITUDES_BACKWARD):
+        batch.set_config(op, B.VARIANT_FUSED)
+    comps = run()
+    want = [[], [], []]
+    for g in range(G):
+        A = np.array([O.amplitudes(widen(U[g]), s) for s in basis])
+        G64 = gy[g].astype(np.complex128)
+        want[0].append(widen(x[g]) @ A)
+        want[1].append(sum(O.amplitude_grad(widen(U[g]), s, np.conj(complex(w)) * G64) for s, w in zip(basis, x[g])).ravel())
+        want[2].append(A.conj() @ G64)
+    for p, q, r in zip(steps, comps, want):
+        assert not np.array_equal(p, q)
+        assert rel_err(p, np.array(r)) <= rel_err(q, np.array(r))
