@@ -1179,16 +1179,33 @@ extern "C" int slos_superposition_create(slos_batch_t components, int G, const i
     std::vector<float> cnorm(std::max(Bt.B, 1), 1.f);
     std::vector<uint32_t> gcols(std::max(G, 1), 0u);
     bool dense = G > 0, sooner[2] = {true, true};
+    int last_n = -1;  // groups mostly come alike: decided once, tables copied
+    int64_t last = -1;
+    for (int g = 0; g < G && dense; ++g) {
+        const int n = Bt.n_host[group_off[g]];
+        const int64_t comps = group_off[g + 1] - group_off[g];
+        if (n == last_n && comps == last) continue;
+        last_n = n;
+        last = comps;
+        dense = comps <= Bt.plan->N[n] && dense_superposition_ok(*Bt.plan, n, comps);
+        for (int d = 0; d < 2 && dense; ++d)
+            sooner[d] = sooner[d] && dense_superposition_sooner(*Bt.plan, n, comps, G, Bt.B, d == 1);
+        dense = dense && (sooner[0] || sooner[1]);
+    }
     std::vector<Counter> ranks;
     std::vector<char> seen;
     for (int n = 0; n <= Bt.n_max && dense; ++n) ranks.emplace_back(Bt.plan->m, n);
     for (int g = 0; g < G && dense; ++g) {
-        const int64_t c0 = group_off[g], c1 = group_off[g + 1];
+        const int64_t c0 = group_off[g], c1 = group_off[g + 1], prev = g > 0 ? group_off[g - 1] : 0;
         const int n = Bt.n_host[c0];
-        dense = c1 - c0 <= Bt.plan->N[n] && dense_superposition_ok(*Bt.plan, n, c1 - c0);
-        if (!dense) break;
-        for (int d = 0; d < 2; ++d)
-            sooner[d] = sooner[d] && dense_superposition_sooner(*Bt.plan, n, c1 - c0, G, Bt.B, d == 1);
+        const int32_t* rows = &Bt.modes_host[(size_t)c0 * kMaxPhotons];
+        if (g > 0 && c0 - prev == c1 - c0 && Bt.n_host[prev] == n &&
+            std::memcmp(rows, rows - (c0 - prev) * kMaxPhotons, (size_t)(c1 - c0) * kMaxPhotons * sizeof(int32_t)) == 0) {
+            std::copy(crank.begin() + prev, crank.begin() + c0, crank.begin() + c0);
+            std::copy(cnorm.begin() + prev, cnorm.begin() + c0, cnorm.begin() + c0);
+            gcols[g] = gcols[g - 1];
+            continue;
+        }
         S->dev.n_present |= 1u << n;
         const Counter& C = ranks[n];
         seen.assign((size_t)Bt.plan->N[n], 0);
