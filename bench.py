@@ -775,10 +775,9 @@ def bench_extension(args, dev):
         out = torch.empty((Bn, Bn), dtype=torch.float32, device=dev)
         step = lambda: B.fock_fidelity_kernel(occ, U, out=out)
         work, unit = Bn * Bn, "kernel entries/s"
-        # M and Glynn's 2^(n-1) terms, on and above the diagonal in tiles of 16 x 16 pairs
-        # (n >= 9: Ryser's 2^n terms for every pair)
-        tiles = (Bn + 15) // 16
-        pairs = 256 * tiles * (tiles + 1) // 2 if n <= 8 else Bn * Bn
+        # M and Glynn's 2^(n-1) terms on and above the diagonal (n >= 9: Ryser's 2^n terms
+        # for every pair)
+        pairs = Bn * (Bn + 1) // 2 if n <= 8 else Bn * Bn
         flop = pairs * (8.0 * n * n * m + 2 ** (n - 1 if n <= 8 else n) * (2 * n + 6 * (n - 1)))
         oracle_one = lambda b: np.array([O.fidelity(Uh[b], Uh[c], occ) for c in range(32)])
         check = lambda b, r: float(np.abs(out[b, :32].cpu().numpy() - r).max())

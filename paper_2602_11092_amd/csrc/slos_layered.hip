@@ -24,8 +24,8 @@
 // n = 8, 16 samples 1502 -> 995, 2766 -> 2140; m = 20, n = 6, 64 samples 265 -> 85, 469 ->
 // 203; m = 14, n = 7, 64 samples 152 -> 68, 306 -> 160; m = 24, n = 8, 1 sample 145 -> 135,
 // 469 -> 333.  The top layers at m = 24, n = 8, 16 samples: the seed fetches 3.6 GB (5.9
-// before) and writes 1.0 in 0.93 ms, the first pull 4.1 (5.4) and 0.26 in 0.70 ms: 5.0
-// and 6.2 TB/s, a large copy's rate; neither more wavefronts nor earlier loads help
+// before) and writes 1.0 in 0.97 ms, the first pull 4.1 (5.4) and 0.26 in 0.73 ms: 4.8
+// and 6.0 TB/s, a large copy's rate; neither more wavefronts nor earlier loads help
 // any further.
 #include "slos_internal.h"
 

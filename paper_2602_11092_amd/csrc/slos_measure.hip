@@ -252,7 +252,8 @@ __global__ __launch_bounds__(kMeasureBlock) void sample_kernel(BatchDev Bt, cons
 // and walks the run's states from p.  Bound by reading p (twice over the L2:
 // once in order, one 64-byte run per shot); the sums that the passes above
 // write and the search reads back are 8 bytes a state.  m = 20, n = 5, B = 512,
-// S = 1024: 34 us (39 with one run of loads in flight per thread); the three passes that form the sums in memory took 165.
+// S = 1024: 24 us (34 with a shot's walk one load after another); the three passes
+// that form the sums in memory took 165.
 constexpr int kRun = 16;
 constexpr int64_t kDirectStates = (int64_t)kRun * 8192;  // run sums within 64 KB of LDS
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
