@@ -476,11 +476,12 @@ def fock_mode_expectations(batch: Batch, U: torch.Tensor, out: Optional[torch.Te
     if out is None:
         out = torch.empty((batch.B, batch.m), dtype=torch.float32, device=U.device)
     _require(out, "out", torch.float32, (batch.B, batch.m))
+    det = _detector(detector)
     if ws is None:
-        ws = batch.workspace(OP_MODE_EXPECTATIONS, U.device, _detector(detector))
+        ws = batch.workspace(OP_MODE_EXPECTATIONS, U.device, det)
     wp, wn = _ws_args(ws)
     _check("fock_mode_expectations_ex",
-           lib().fock_mode_expectations_ex(batch.handle, _ptr(U), _ptr(out), _detector(detector), wp, wn,
+           lib().fock_mode_expectations_ex(batch.handle, _ptr(U), _ptr(out), det, wp, wn,
                                            _stream_ptr(U.device)))
     return out
 
@@ -493,12 +494,13 @@ def fock_mode_expectations_backward(batch: Batch, U: torch.Tensor, grad_out: tor
     if out is None:
         out = torch.empty_like(U)
     _require(out, "grad_U", torch.complex64, (batch.B, batch.m, batch.m))
+    det = _detector(detector)
     if ws is None:
-        ws = batch.workspace(OP_MODE_EXPECTATIONS_BACKWARD, U.device, _detector(detector))
+        ws = batch.workspace(OP_MODE_EXPECTATIONS_BACKWARD, U.device, det)
     wp, wn = _ws_args(ws)
     _check("fock_mode_expectations_backward_ex",
            lib().fock_mode_expectations_backward_ex(batch.handle, _ptr(U), _ptr(grad_out), _ptr(out),
-                                                    _detector(detector), wp, wn, _stream_ptr(U.device)))
+                                                    det, wp, wn, _stream_ptr(U.device)))
     return out
 
 
