@@ -42,7 +42,7 @@ constexpr int kDenseBlock = 128;
 struct DenseLayout {
     uint32_t T[kMaxPhotons + 1];     // T_k, float2 [N_k][N_{n-k}]
     uint32_t g[2], gn;               // gT_k at g[k & 1] for k < n, and gT_n, double2 (backward)
-    uint32_t U;                      // float2 [m][m]
+    uint32_t U;                      // double2 [m][m], widened once
     uint32_t part;                   // double2 [kDenseBlock]: partial sums of gU (backward)
     uint32_t succ[kMaxPhotons + 1];  // uint16 [N_{l-1}][m], l = 1..n: rank of I' + e_i
     uint32_t pred[kMaxPhotons + 1];  // uint16 [N_l][l][2], l = 1..n: mode and rank of the removals, mode 0xFFFF: none
@@ -68,8 +68,9 @@ __host__ __device__ inline void dense_layout(const int* N, int m, int n, bool bw
     }
     L.part = at;
     at += bwd ? 16u * kDenseBlock : 0;
+    at = (at + 15u) & ~15u;
     L.U = at;
-    at += 8u * (uint32_t)(m * m);
+    at += 16u * (uint32_t)(m * m);
     for (int l = 1; l <= n; ++l) {
         L.succ[l] = at;
         at += (2u * (uint32_t)(N[l - 1] * m) + 3u) & ~3u;
@@ -98,11 +99,11 @@ struct DenseArgs {
     float2* gx;              // [C] or nullptr (backward)
 };
 
-__device__ __forceinline__ void z_fma_conj(double2& acc, float2 a, double2 b) {  // acc += conj(a) b
-    acc.x = fma((double)a.x, b.x, acc.x);
-    acc.x = fma((double)a.y, b.y, acc.x);
-    acc.y = fma((double)a.x, b.y, acc.y);
-    acc.y = fma(-(double)a.y, b.x, acc.y);
+__device__ __forceinline__ void z_fma_conj(double2& acc, double2 a, double2 b) {  // acc += conj(a) b
+    acc.x = fma(a.x, b.x, acc.x);
+    acc.x = fma(a.y, b.y, acc.x);
+    acc.y = fma(a.x, b.y, acc.y);
+    acc.y = fma(-a.y, b.x, acc.y);
 }
 
 // prod t! of the state whose n removals are pred (a mode's further photons are
@@ -130,10 +131,12 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
     for (int k = 0; k <= kMaxPhotons; ++k) N[k] = k <= n ? (int)ldc(&A.Ls[k].N) : 0;
     DenseLayout L;
     dense_layout(N, m, n, BWD, L);
-    float2* U = (float2*)(dlds + L.U);
+    double2* U = (double2*)(dlds + L.U);
     // U with the columns no component uses left out (they may hold anything)
-    for (int e = tid; e < m * m; e += kDenseBlock)
-        U[e] = (cols >> (e % m)) & 1 ? A.U[(size_t)g * m * m + e] : c_zero();
+    for (int e = tid; e < m * m; e += kDenseBlock) {
+        const float2 v = (cols >> (e % m)) & 1 ? A.U[(size_t)g * m * m + e] : c_zero();
+        U[e] = make_double2(v.x, v.y);
+    }
     float2* T0 = (float2*)(dlds + L.T[0]);
     for (int e = tid; e < N[n]; e += kDenseBlock) T0[e] = c_zero();
     for (int l = 1; l <= n; ++l) {
@@ -166,15 +169,16 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
         const int cols_n = N[n - k - 1], cols_k = N[n - k];
         for (int e = tid; e < N[k + 1] * cols_n; e += kDenseBlock) {
             const int r = e / cols_n, q = e % cols_n;
-            const float2* u = U + pred[2 * r * (k + 1)] * m;
+            const double2* u = U + pred[2 * r * (k + 1)] * m;
             const float2* t = Tk + pred[2 * r * (k + 1) + 1] * cols_k;
             double2 acc = make_double2(0.0, 0.0);
             for (int i = 0; i < m; ++i) {
-                const float2 a = u[i], v = t[succ[q * m + i]];
-                acc.x = fma((double)a.x, (double)v.x, acc.x);
-                acc.x = fma(-(double)a.y, (double)v.y, acc.x);
-                acc.y = fma((double)a.x, (double)v.y, acc.y);
-                acc.y = fma((double)a.y, (double)v.x, acc.y);
+                const double2 a = u[i];
+                const float2 v = t[succ[q * m + i]];
+                acc.x = fma(a.x, (double)v.x, acc.x);
+                acc.x = fma(-a.y, (double)v.y, acc.x);
+                acc.y = fma(a.x, (double)v.y, acc.y);
+                acc.y = fma(a.y, (double)v.x, acc.y);
             }
             Tn[e] = make_float2((float)acc.x, (float)acc.y);
         }
@@ -220,7 +224,8 @@ __global__ __launch_bounds__(kDenseBlock) void dense_kernel(DenseArgs A) {
                 for (int r = lo; r < hi; ++r) {
                     const float2* t = Tk + predJ[2 * r * (k + 1) + 1] * cols_k;
                     for (int q = part; q < cols_n; q += parts) {
-                        z_fma_conj(gu[w], t[succI[q * m + i]], gu1[r * cols_n + q]);
+                        const float2 a = t[succI[q * m + i]];
+                        z_fma_conj(gu[w], make_double2(a.x, a.y), gu1[r * cols_n + q]);
                     }
                 }
             }
